@@ -333,7 +333,7 @@ hipError_t launch_m3_fwd(const float* Zt, int32_t Bp, int32_t B, const float* W2
 //   dZ[b][n] = dH[b][n] * act'(Z[b][n])                  (in place over Zt)
 //   dW2[o][n] = sum_b G[mid[n]][b][o] * act(Z[b][n])
 //   W2[o][n] -= lr * dW2[o][n]        (or dW2 stored, gradient mode)
-// One wave per run of kT5 consecutive hidden units and the whole batch.
+// One wave per run of `run` consecutive hidden units and the whole batch.
 // Lanes as in the forward (groups of LG lanes per hidden unit, four samples
 // per lane), with `slots` passes when the batch is wider than 256.  The
 // wave walks the segments of its run, so the model (its G rows, held in
@@ -342,7 +342,15 @@ hipError_t launch_m3_fwd(const float* Zt, int32_t Bp, int32_t B, const float* W2
 // passes; W2 is updated once at the end.
 // ---------------------------------------------------------------------------
 
-static constexpr int kT5 = 256;
+// Units per wave: at most kRunMax (long runs reload G and the segment data
+// least), halved down to kRunMin until the launch has kRunWaves waves.  A wave
+// walks its run one segment and one pass of the batch after the other, so a
+// launch of few waves lasts as long as one of them and leaves the memory
+// idle: with 256 units per wave at 201,000 units and 1,024 samples (785 waves)
+// it took 1096 us for 1.65 GB; with 16, a step there takes 0.79 ms less, and
+// one of 51,000 units and 1,000 samples 0.46 ms instead of 1.23.
+static constexpr int kRunMax = 256, kRunMin = 16;
+static constexpr int64_t kRunWaves = 16384;
 
 template <int OM, int A, bool ZB>
 __device__ __forceinline__ void bwd_segment(float* __restrict__ Zt,
@@ -411,14 +419,14 @@ __global__ __launch_bounds__(kBlock) void k_m3_bwd(
     float* __restrict__ W2,
     int64_t N, int64_t ldw, int O, const int32_t* __restrict__ mid,
     const int64_t* __restrict__ seg_off, const int32_t* __restrict__ act,
-    const float* __restrict__ G, int LG, int slots, float lr, const float* __restrict__ lrm,
-    float* __restrict__ dW2) {
-  __shared__ float lds[4 * kT5 * OM];
+    const float* __restrict__ G, int LG, int slots, int run, float lr,
+    const float* __restrict__ lrm, float* __restrict__ dW2) {
+  extern __shared__ float lds[];  // [4][run][OM]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  float* dwl = lds + wave * kT5 * OM;
-  const int64_t r0 = ((int64_t)blockIdx.x * 4 + wave) * kT5;
-  int64_t r1 = r0 + kT5;
+  float* dwl = lds + wave * run * OM;
+  const int64_t r0 = ((int64_t)blockIdx.x * 4 + wave) * run;
+  int64_t r1 = r0 + run;
   if (r1 > N) r1 = N;
   const int NG = 64 / LG;
   const int g = lane / LG;
@@ -488,20 +496,23 @@ static void m3_bwd_dispatch(float* Zt, bool zb, unsigned short* dZ16, int32_t Bp
     while (LG < q) LG <<= 1;
   }
   const int slots = ceil_div_i(Bp, 4 * LG);
-  const int64_t waves = (N + kT5 - 1) / kT5;
+  int run = kRunMax;
+  while (run > kRunMin && N < kRunWaves * run) run >>= 1;
+  const size_t lds = (size_t)4 * run * OM * sizeof(float);
+  const int64_t waves = (N + run - 1) / run;
   const unsigned blocks = (unsigned)((waves + 3) / 4);
   if (dW2 && zb)
-    k_m3_bwd<OM, true, true><<<blocks, kBlock, 0, s>>>(Zt, dZ16, Bp, W2, N, ldw, O, mid, seg_off,
-                                                       act, G, LG, slots, lr, lrm, dW2);
+    k_m3_bwd<OM, true, true><<<blocks, kBlock, lds, s>>>(Zt, dZ16, Bp, W2, N, ldw, O, mid, seg_off,
+                                                       act, G, LG, slots, run, lr, lrm, dW2);
   else if (dW2)
-    k_m3_bwd<OM, true, false><<<blocks, kBlock, 0, s>>>(Zt, dZ16, Bp, W2, N, ldw, O, mid, seg_off,
-                                                        act, G, LG, slots, lr, lrm, dW2);
+    k_m3_bwd<OM, true, false><<<blocks, kBlock, lds, s>>>(Zt, dZ16, Bp, W2, N, ldw, O, mid, seg_off,
+                                                        act, G, LG, slots, run, lr, lrm, dW2);
   else if (zb)
-    k_m3_bwd<OM, false, true><<<blocks, kBlock, 0, s>>>(Zt, dZ16, Bp, W2, N, ldw, O, mid, seg_off,
-                                                        act, G, LG, slots, lr, lrm, dW2);
+    k_m3_bwd<OM, false, true><<<blocks, kBlock, lds, s>>>(Zt, dZ16, Bp, W2, N, ldw, O, mid, seg_off,
+                                                        act, G, LG, slots, run, lr, lrm, dW2);
   else
-    k_m3_bwd<OM, false, false><<<blocks, kBlock, 0, s>>>(Zt, dZ16, Bp, W2, N, ldw, O, mid, seg_off,
-                                                         act, G, LG, slots, lr, lrm, dW2);
+    k_m3_bwd<OM, false, false><<<blocks, kBlock, lds, s>>>(Zt, dZ16, Bp, W2, N, ldw, O, mid, seg_off,
+                                                         act, G, LG, slots, run, lr, lrm, dW2);
 }
 
 hipError_t launch_m3_bwd(float* Zt, unsigned short* dZ16, int32_t Bp, float* W2, int64_t N,
