@@ -169,6 +169,27 @@ hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Rows of `cols` floats between two row strides (parameters between their
+// padded device rows and the caller's contiguous ones).
+__global__ __launch_bounds__(kBlock) void k_copy_rows(float* __restrict__ dst, int64_t ldd,
+                                                      const float* __restrict__ src, int64_t lds,
+                                                      int64_t rows, int cols) {
+  const int64_t total = rows * cols;
+  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < total;
+       i += (int64_t)gridDim.x * kBlock) {
+    const int64_t r = i / cols;
+    const int64_t c = i - r * cols;
+    dst[r * ldd + c] = src[r * lds + c];
+  }
+}
+
+hipError_t launch_copy_rows(float* dst, int64_t ldd, const float* src, int64_t lds, int64_t rows,
+                            int32_t cols, hipStream_t s) {
+  if (rows <= 0 || cols <= 0) return hipSuccess;
+  k_copy_rows<<<grid_for(rows * cols), kBlock, 0, s>>>(dst, ldd, src, lds, rows, cols);
+  return hipGetLastError();
+}
+
 // Zero the weights of the input features a model does not see (run when
 // the masks or the weights are set; the SGD steps then keep them at zero).
 __global__ __launch_bounds__(kBlock) void k_apply_fmask(float* __restrict__ W1, int64_t total,

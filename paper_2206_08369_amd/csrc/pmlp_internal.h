@@ -239,6 +239,10 @@ hipError_t launch_hidden_out(const float* Zt, int32_t Bp, int32_t B, int64_t N,
 
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t s);
 
+// dst[r ldd + c] = src[r lds + c] for r < rows, c < cols.
+hipError_t launch_copy_rows(float* dst, int64_t ldd, const float* src, int64_t lds, int64_t rows,
+                            int32_t cols, hipStream_t s);
+
 // Two hidden layers per model (Section 7, Figure 3).  Model m has h1[m]
 // first-layer units (rows off1[m].. of Zt1), h2[m] second-layer units (rows
 // off2[m].. of Zt2) and the hidden-to-hidden block W12[koff[m] ..] of
