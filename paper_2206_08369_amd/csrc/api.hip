@@ -1453,8 +1453,8 @@ int pmlp_create_deep(pmlp_t* out, int32_t F, int32_t O, int32_t M, const int32_t
   std::vector<SegUnit> ufwd, uback;
   std::vector<SegTile> tgrad;
   for (int32_t m = 0; m < M; ++m) {
-    for (int32_t r = 0; r < h2[m]; r += 8) ufwd.push_back(SegUnit{m, r});
-    for (int32_t r = 0; r < h1[m]; r += 8) uback.push_back(SegUnit{m, r});
+    for (int32_t r = 0; r < h2[m]; r += 16) ufwd.push_back(SegUnit{m, r});
+    for (int32_t r = 0; r < h1[m]; r += 16) uback.push_back(SegUnit{m, r});
     for (int32_t i = 0; i < h2[m]; i += 16)
       for (int32_t j = 0; j < h1[m]; j += 64) tgrad.push_back(SegTile{m, i, j, 0});
   }

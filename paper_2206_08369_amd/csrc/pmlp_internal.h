@@ -256,7 +256,7 @@ struct DeepArgs {
   const int32_t* act;   // [M]
   const float* W12;     // [K]
 };
-struct SegUnit {   // rows r0 .. r0+7 (those that exist) of one layer of model m
+struct SegUnit {   // rows r0 .. r0+15 (those that exist) of one layer of model m
   int32_t m, r0;
 };
 struct SegTile {   // rows i0 .. i0+15, columns j0 .. j0+63 of model m's W12 block
