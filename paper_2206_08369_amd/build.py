@@ -15,8 +15,12 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libpmlp.so")
-SOURCES = ("k_misc.hip", "k_gemm.hip", "k_gemm_bf16.hip", "k_m3.hip", "k_lds.hip", "k_deep.hip",
-           "api.hip")
+# (source, extra flags); the batch-resident kernels are compiled once per
+# padded batch size
+SOURCES = [("k_lds.hip", [])]
+SOURCES += [("k_fwd_s.hip", ["-DPMLP_FWD_BP=%d" % bp]) for bp in (256, 128, 64, 32, 16)]
+SOURCES += [(s, []) for s in ("k_gemm_bf16.hip", "k_m3.hip", "k_misc.hip", "k_gemm.hip", "k_deep.hip",
+                              "api.hip")]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -51,11 +55,11 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
     os.makedirs(objdir, exist_ok=True)
     tag = "%d" % os.getpid()
     objs, cmds = [], []
-    for src in SOURCES:
-        obj = os.path.join(objdir, src.replace(".hip", ".%s.o" % tag))
+    for i, (src, extra) in enumerate(SOURCES):
+        obj = os.path.join(objdir, src.replace(".hip", ".%d.%s.o" % (i, tag)))
         objs.append(obj)
-        cmds.append([hipcc()] + HIPCC_FLAGS + ["-I", INCLUDE, "-I", CSRC, "-c",
-                                               os.path.join(CSRC, src), "-o", obj])
+        cmds.append([hipcc()] + HIPCC_FLAGS + extra + ["-I", INCLUDE, "-I", CSRC, "-c",
+                                                       os.path.join(CSRC, src), "-o", obj])
     jobs = jobs or min(len(cmds), max(1, os.cpu_count() or 1))
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         results = list(ex.map(lambda c: _run(c, verbose), cmds))

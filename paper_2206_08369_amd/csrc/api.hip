@@ -97,6 +97,16 @@ struct PmlpDeep {
   float* Zt2 = nullptr;       // [N2pad][Bp]
 };
 
+// How a batch class (a padded batch size up to 256) divides the pack for
+// k_fwd_s: groups of whole models, widest first.
+struct StepPlan {
+  int slots = 0;                   // workgroups of k_fwd_s the device holds (0: no instance)
+  int32_t ngroups = 0;
+  const StepGroup* groups = nullptr;  // in the handle's one allocation
+};
+constexpr int kStepClasses = 5;
+constexpr int32_t kStepBatch[kStepClasses] = {16, 32, 64, 128, 256};
+
 struct pmlp {
   int dev = 0;
   hipStream_t stream = nullptr;
@@ -115,6 +125,10 @@ struct pmlp {
   int32_t* d_act = nullptr;
   int32_t* d_mid = nullptr;   // [Npad] model of each hidden unit
   int32_t* d_actn = nullptr;  // [Npad] activation id of each hidden unit
+  int32_t* d_uinfo = nullptr; // [Npad] the same, + 256 at the last unit of a model
+  StepPlan plan[kStepClasses];
+  StepGroup* d_groups = nullptr;
+  int32_t widest = 0;  // units of the widest model
   Tile3* d_tiles = nullptr;
   int32_t* d_order = nullptr;  // tile indices, widest first
   int32_t ntiles = 0;
@@ -167,6 +181,8 @@ void release(pmlp* h) {
   dfree(h->d_act);
   dfree(h->d_mid);
   dfree(h->d_actn);
+  dfree(h->d_uinfo);
+  dfree(h->d_groups);
   dfree(h->d_tiles);
   dfree(h->d_order);
   dfree(h->loss);
@@ -252,6 +268,12 @@ int use_device(pmlp* h) {
   PMLP_HIP(hipGetDevice(&cur));
   if (cur != h->dev) PMLP_HIP(hipSetDevice(h->dev));
   return PMLP_OK;
+}
+
+int step_class(int32_t Bp) {
+  for (int c = 0; c < kStepClasses; ++c)
+    if (kStepBatch[c] == Bp) return c;
+  return -1;
 }
 
 int ensure_workspace(pmlp* h, int32_t Bp) {
@@ -456,6 +478,8 @@ int check_batch(pmlp* h, const void* X, int32_t B) {
   return PMLP_OK;
 }
 
+int32_t div_up(int64_t a, int64_t b) { return (int32_t)((a + b - 1) / b); }
+
 // Batch padding: a multiple of 16, and a power of two up to 256 so that the
 // LDS-resident forward GEMM has an instance for it.
 int32_t pad_batch(int32_t B) {
@@ -466,6 +490,174 @@ int32_t pad_batch(int32_t B) {
     Bp = p;
   }
   return Bp;
+}
+
+// ---- the sample-split forward ------------------------------------------------
+
+#define PMLP_BY_BATCH(c, call)   \
+  switch (kStepBatch[c]) {       \
+    case 16: return call(16);    \
+    case 32: return call(32);    \
+    case 64: return call(64);    \
+    case 128: return call(128);  \
+    default: return call(256);   \
+  }
+
+int fwd_s_slots(int c, int32_t F4, int32_t O) {
+#define PMLP_CALL(BP) fwd_s_slots_##BP(F4, O)
+  PMLP_BY_BATCH(c, PMLP_CALL)
+#undef PMLP_CALL
+}
+
+hipError_t launch_fwd_s(int c, const FwdSArgs& a, hipStream_t s) {
+  note_variant("k_fwd_s", kArithX3);
+#define PMLP_CALL(BP) launch_fwd_s_##BP(a, s)
+  PMLP_BY_BATCH(c, PMLP_CALL)
+#undef PMLP_CALL
+}
+
+// Runs of whole models for `slots` workgroups: the widest of at most k
+// `slots` runs as narrow as can be, k such that a run is about kStepGroup
+// units at most.  A model costs its units and about three more (its reduction
+// and its logits).
+constexpr int64_t kStepGroup = 1024;
+constexpr int64_t kSplitUnits = 1024;
+
+std::vector<StepGroup> step_groups(const std::vector<int32_t>& hs, int64_t N, int slots) {
+  constexpr int64_t kModel = 3;
+  const int64_t total = N + kModel * (int64_t)hs.size();
+  const int64_t k = ((total + slots - 1) / slots + kStepGroup - 1) / kStepGroup;
+  const int64_t want = k * slots;
+  auto runs = [&](int64_t cap) {  // of at most cap, filled in order
+    int64_t n = 1, at = 0;
+    for (const int32_t w : hs) {
+      if (at > 0 && at + w + kModel > cap) {
+        ++n;
+        at = 0;
+      }
+      at += w + kModel;
+    }
+    return n;
+  };
+  const int64_t widest = *std::max_element(hs.begin(), hs.end()) + kModel;
+  int64_t lo = std::max((total + want - 1) / want, widest), hi = lo + widest;
+  while (runs(hi) > want) hi += widest;
+  while (hi - lo > lo / 64) {  // (to a sixty-fourth: a pass over the models each)
+    const int64_t mid = lo + (hi - lo) / 2;
+    if (runs(mid) <= want) hi = mid;
+    else lo = mid + 1;
+  }
+  std::vector<StepGroup> g;
+  StepGroup cur{0, 0, 0, 0, 0};
+  int64_t n = 0;
+  for (size_t m = 0; m < hs.size(); ++m) {
+    if (cur.nm > 0 && cur.len + hs[m] + kModel * (cur.nm + 1) > hi) {
+      g.push_back(cur);
+      cur.nm = 0;
+    }
+    if (cur.nm == 0) cur = StepGroup{n, 0, (int32_t)m, 0, (int32_t)g.size()};
+    cur.len += hs[m];
+    ++cur.nm;
+    n += hs[m];
+  }
+  g.push_back(cur);
+  std::stable_sort(g.begin(), g.end(),
+                   [](const StepGroup& x, const StepGroup& y) { return x.len > y.len; });
+  return g;
+}
+
+// The plans of every batch class whose kernels take this pack's shape.
+int build_step_plans(pmlp* h) {
+  h->widest = *std::max_element(h->hs.begin(), h->hs.end());
+  std::vector<StepGroup> all;
+  size_t at[kStepClasses] = {};
+  for (int c = 0; c < kStepClasses; ++c) {
+    if (kStepBatch[c] >= 64 && h->N < kSplitUnits) break;
+    StepPlan& p = h->plan[c];
+    p.slots = fwd_s_slots(c, h->F4, h->O);
+    if (p.slots <= 0) continue;
+    const std::vector<StepGroup> g = step_groups(h->hs, h->N, p.slots);
+    at[c] = all.size();
+    all.insert(all.end(), g.begin(), g.end());
+    p.ngroups = (int32_t)g.size();
+  }
+  if (all.empty()) return PMLP_OK;
+  if (hipMalloc(&h->d_uinfo, (size_t)h->Npad * sizeof(int32_t)) != hipSuccess ||
+      hipMalloc(&h->d_groups, all.size() * sizeof(StepGroup)) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(PMLP_ENOMEM, "device allocation failed for the step plans");
+  }
+  PMLP_HIP(hipMemcpy(h->d_groups, all.data(), all.size() * sizeof(StepGroup),
+                     hipMemcpyHostToDevice));
+  PMLP_HIP(launch_unit_info(h->d_mid, h->d_actn, h->N, h->Npad, h->d_uinfo, h->stream));
+  PMLP_HIP(hipStreamSynchronize(h->stream));
+  for (int c = 0; c < kStepClasses; ++c) h->plan[c].groups = h->d_groups + at[c];
+  return PMLP_OK;
+}
+
+// Whether batch class c has the sample-split kernels at all.
+bool has_split_kernels(const pmlp* h, int c) {
+  if (c < 0 || !h->lds_kernels || bf16_mode(h) || h->deep || h->plan[c].slots <= 0) return false;
+  return !(h->fused_forward && fwd_m3_supported(kStepBatch[c], h->F4, h->O));
+}
+
+// How many units wide a model may be before its workgroup, which takes it
+// alone, is what the launch waits for: what the rest of the launch hides
+// (units x samples / 50,000) and a term for launches saved.  Measured where a
+// model of w units takes 0.1 w + 8 us through k_fwd_s: 100 features, widths up to 1,000, us before and after:
+// 80,000 units x 256, 102 / 109 (stays); 300,000 x 256, 224 / 162; 300,000 x
+// 64, 111 / 121 (stays) and widths up to 400, 83 / 63.
+int64_t split_reach(const pmlp* h, int c, int64_t nchunk) {
+  return h->N * kStepBatch[c] * nchunk / 50000;
+}
+
+// Whether a forward pass over nchunk batches of class c runs as k_fwd_s.  (The
+// term: widths up to 64 and 100 in packs of 1,000 to 20,000 units, batch of
+// 16: 19 us / 11 and 19 / 16; up to 200, 20 / 24.)
+bool fwd_split(const pmlp* h, int c, int64_t nchunk) {
+  return has_split_kernels(h, c) && h->widest <= 128 + split_reach(h, c, nchunk);
+}
+
+// Whether a training step of class c runs on the sample-split kernels.  (The
+// term: packs of 5,000 units, widths up to 100 and batches of 16, 23 us / 24;
+// up to 200 and 256, 77 / 66; up to 400, 81 / 105.)  Models of fewer than four
+// units on average are as fast or faster on unit-split kernels once the pack
+// fills the chip: several models to a tile are several passes over its sums
+// (100 features, batch of 256, 130,000 units: 373 us / 452; 20,000: 120 / 104).
+bool train_split(const pmlp* h, int c) {
+  if (!has_split_kernels(h, c)) return false;
+  const int64_t zs = h->N * kStepBatch[c];
+  if (h->O <= 2 && h->N < 4 * (int64_t)h->M && zs > 6000000) return false;
+  return h->widest <= 64 + kStepBatch[c] / 2 + split_reach(h, c, 1);
+}
+
+// The sample-split forward of B samples in nchunk batches of class c: Zt
+// and/or logits out[m sm + b sb + o].
+int forward_split(pmlp* h, int c, const float* X, int32_t B, int32_t nchunk, float* Zt, float* out,
+                  int64_t sm, int64_t sb) {
+  const StepPlan& p = h->plan[c];
+  FwdSArgs f{};
+  f.X = X;
+  f.B = B;
+  f.F = h->F;
+  f.F4 = h->F4;
+  f.O = h->O;
+  f.bcol = h->bcol;
+  f.nchunk = nchunk;
+  f.wpc = std::max(1, std::min(p.slots / nchunk, p.ngroups));
+  f.W1 = h->W1;
+  f.W2 = h->W2;
+  f.ldw = h->Npad;
+  f.b2 = h->b2;
+  f.mid = h->d_mid;
+  f.uinfo = h->d_uinfo;
+  f.groups = p.groups;
+  f.ngroups = p.ngroups;
+  f.Zt = Zt;
+  f.out = out;
+  f.sm = sm;
+  f.sb = sb;
+  return run(h, KID_FWD_M3, [&] { return launch_fwd_s(c, f, h->stream); });
 }
 
 // Batch copy and the input-to-hidden product (Section 3, step 1).
@@ -592,10 +784,17 @@ int step(pmlp* h, const float* X, const void* y, int32_t B, float lr, const floa
          const Work* work = nullptr) {
   const int32_t Bp = pad_batch(B);
   if (int rc = use_device(h)) return rc;
+  const int cls = step_class(Bp);
   if (!work)
     if (int rc = ensure_workspace(h, Bp)) return rc;
   const Work w = work ? *work : handle_work(h);
-  if (forward_fused(h, Bp)) {
+  if (train_split(h, cls)) {
+    if (int rc = run(h, KID_PACK_X, [&] {  // Xt, for the backward
+          return launch_pack_x(X, B, h->F, Bp, h->F4, h->bcol, w.Xp, w.Xt, h->stream);
+        }))
+      return rc;
+    if (int rc = forward_split(h, cls, X, B, 1, w.Zt, w.LG, (int64_t)Bp * h->O, h->O)) return rc;
+  } else if (forward_fused(h, Bp)) {
     if (int rc = forward_m3(h, X, B, Bp, w, w.LG, (int64_t)Bp * h->O, h->O,
                             (int64_t)h->M * Bp * h->O))
       return rc;
@@ -1019,6 +1218,7 @@ int pmlp_create_ex(pmlp_t* out, int32_t F, int32_t O, int32_t M, const int32_t* 
                        hipMemcpyHostToDevice));
     PMLP_HIP(hipMemcpy(h->d_actn, actn.data(), (size_t)Npad * sizeof(int32_t),
                        hipMemcpyHostToDevice));
+    if (int rc = build_step_plans(h)) return rc;
     PMLP_HIP(hipMemset(h->W1, 0, w1_bytes));
     PMLP_HIP(hipMemset(h->W2, 0, (size_t)O * Npad * sizeof(float)));
     PMLP_HIP(hipMemcpy(h->d_tiles, tiles.data(), tiles.size() * sizeof(Tile3),
@@ -1079,6 +1279,23 @@ int pmlp_forward(pmlp_t h, const float* X_dev, int32_t B, float* logits_dev) {
   if (!logits_dev) return fail(PMLP_EINVAL, "null logits");
   const int32_t Bp = pad_batch(B);
   if (int rc = use_device(h)) return rc;
+  {
+    // one launch, whatever the batch: runs of 256 samples (or of 128 or 64
+    // where that pads the batch less)
+    int cls = step_class(Bp);
+    int32_t nchunk = 1;
+    if (cls < 0) {
+      cls = kStepClasses - 1;
+      for (int c = kStepClasses - 2; c >= 2; --c)
+        if ((int64_t)div_up(B, kStepBatch[c]) * kStepBatch[c] <
+            (int64_t)div_up(B, kStepBatch[cls]) * kStepBatch[cls])
+          cls = c;
+      nchunk = div_up(B, kStepBatch[cls]);
+    }
+    if (fwd_split(h, cls, nchunk))
+      return forward_split(h, cls, X_dev, B, nchunk, nullptr, logits_dev, h->O,
+                           (int64_t)h->M * h->O);
+  }
   if (int rc = ensure_workspace(h, Bp)) return rc;
   if (PmlpDeep* d = h->deep) {
     if (int rc = ensure_deep_workspace(h, Bp)) return rc;
@@ -1231,7 +1448,12 @@ int pmlp_hidden(pmlp_t h, const float* X_dev, int32_t B, float* Z_dev, float* H_
   const int32_t Bp = pad_batch(B);
   if (int rc = use_device(h)) return rc;
   if (int rc = ensure_workspace(h, Bp)) return rc;
-  if (int rc = forward_hidden(h, X_dev, B, Bp, handle_work(h))) return rc;
+  if (const int cls = step_class(Bp); train_split(h, cls)) {
+    // the same Z, bit for bit, as this batch's training step and forward use
+    if (int rc = forward_split(h, cls, X_dev, B, 1, h->Zt, nullptr, 0, 0)) return rc;
+  } else if (int rc = forward_hidden(h, X_dev, B, Bp, handle_work(h))) {
+    return rc;
+  }
   if (!Z_dev && !H_dev) return PMLP_OK;
   return run(h, KID_ACT, [&] {
     return launch_hidden_out(h->Zt, Bp, B, h->N, h->d_mid, h->d_act, Z_dev, H_dev, h->stream,

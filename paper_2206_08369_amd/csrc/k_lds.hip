@@ -275,43 +275,6 @@ __global__ __launch_bounds__(kLdsBlock) void k_fwd_lds_ring(FwdLdsArgs a) {
 
 static constexpr int kX3RemMax = 7;  // fp32 remainder steps: K mod 32 <= 28
 
-// two values at a time: one packed conversion per piece, the pieces read
-// back as floats from the low and high halves
-__device__ __forceinline__ uint32_t bf16_pair(f32x2 v) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-__device__ __forceinline__ f32x2 bf16_pair_value(uint32_t p) {
-  return f32x2{__builtin_bit_cast(float, p << 16), __builtin_bit_cast(float, p & 0xffff0000u)};
-}
-
-__device__ __forceinline__ void split3(const f32x4& a, const f32x4& b, bf16x8& p0, bf16x8& p1,
-                                       bf16x8& p2) {
-  uint32_t q0[4], q1[4], q2[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const f32x2 x = j < 2 ? f32x2{a[2 * j], a[2 * j + 1]} : f32x2{b[2 * j - 4], b[2 * j - 3]};
-    q0[j] = bf16_pair(x);
-    const f32x2 r1 = x - bf16_pair_value(q0[j]);
-    q1[j] = bf16_pair(r1);
-    q2[j] = bf16_pair(r1 - bf16_pair_value(q1[j]));
-  }
-  p0 = __builtin_bit_cast(bf16x8, q0);
-  p1 = __builtin_bit_cast(bf16x8, q1);
-  p2 = __builtin_bit_cast(bf16x8, q2);
-}
-
-// acc += a b for one 32-wide k chunk, smallest piece products first
-__device__ __forceinline__ f32x4 mfma_x3(const bf16x8& a0, const bf16x8& a1, const bf16x8& a2,
-                                         const bf16x8& b0, const bf16x8& b1, const bf16x8& b2,
-                                         f32x4 acc) {
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2, b0, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b2, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b0, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b1, acc, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b0, acc, 0, 0, 0);
-}
-
 // Product k (0..5) of mfma_x3, in the same order.
 __device__ __forceinline__ f32x4 mfma_x3_step(int k, const bf16x8& a0, const bf16x8& a1,
                                               const bf16x8& a2, const bf16x8& b0,

@@ -169,6 +169,24 @@ hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t s) {
   return hipGetLastError();
 }
 
+__global__ __launch_bounds__(kBlock) void k_unit_info(const int32_t* __restrict__ mid,
+                                                      const int32_t* __restrict__ actn, int64_t N,
+                                                      int64_t Npad, int32_t* __restrict__ info) {
+  for (int64_t n = (int64_t)blockIdx.x * kBlock + threadIdx.x; n < Npad;
+       n += (int64_t)gridDim.x * kBlock) {
+    const bool last = n + 1 >= N || mid[n + 1] != mid[n];
+    info[n] = n < N ? actn[n] + (last ? 256 : 0) : 0;
+  }
+}
+
+hipError_t launch_unit_info(const int32_t* mid, const int32_t* actn, int64_t N, int64_t Npad,
+                            int32_t* info, hipStream_t s) {
+  note_variant("k_unit_info", kArithNone);
+  if (Npad <= 0) return hipSuccess;
+  k_unit_info<<<grid_for(Npad), kBlock, 0, s>>>(mid, actn, N, Npad, info);
+  return hipGetLastError();
+}
+
 // Rows of `cols` floats between two row strides (parameters between their
 // padded device rows and the caller's contiguous ones).
 __global__ __launch_bounds__(kBlock) void k_copy_rows(float* __restrict__ dst, int64_t ldd,

@@ -177,6 +177,63 @@ struct BwdArgs {
 bool bwd_lds_supported(int32_t Bp, int32_t F4, int32_t O);
 hipError_t launch_bwd_lds(const BwdArgs& a, hipStream_t s);
 
+// Workgroups of a kernel the current device holds at once; 0 if its dynamic
+// LDS does not fit (and the kernel then allows that much).
+inline int resident_blocks(const void* fn, int threads, size_t lds) {
+  int dev = 0, cus = 0, lmax = 0, per = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipDeviceGetAttribute(&lmax, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
+      lds > (size_t)lmax ||
+      hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, threads, lds) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  return per * cus;
+}
+
+// Groups of whole models, the work units of k_fwd_s.
+struct StepGroup {
+  int64_t n0;           // first hidden unit
+  int32_t len;          // hidden units
+  int32_t m0, nm;       // first model, number of models
+  int32_t rank;         // place among the groups in unit order
+};
+
+// The forward pass with the waves split over the samples (k_fwd_s): logits
+//   out[m sm + b sb + o], and Zt [Npad][Bp] where set (one of the two at least;
+// more than Bp samples only without Zt).
+struct FwdSArgs {
+  const float* X;    // [B][F]
+  int32_t B, F, F4, O, bcol;
+  int32_t nchunk;    // batches of Bp samples in B
+  int32_t wpc;       // workgroups per such batch
+  const float* W1;   // [Npad][F4]
+  const float* W2;   // [O][ldw]
+  int64_t ldw;
+  const float* b2;   // [M][O] or null
+  const int32_t* mid;    // [Npad] model of each unit
+  const int32_t* uinfo;  // [Npad] activation id, + 256 at a model's last unit
+  const StepGroup* groups;
+  int32_t ngroups;
+  float* Zt;
+  float* out;
+  int64_t sm, sb;
+};
+#define PMLP_FWD_S_DECL(BP)                    \
+  int fwd_s_slots_##BP(int32_t F4, int32_t O); \
+  hipError_t launch_fwd_s_##BP(const FwdSArgs& a, hipStream_t s);
+PMLP_FWD_S_DECL(16)
+PMLP_FWD_S_DECL(32)
+PMLP_FWD_S_DECL(64)
+PMLP_FWD_S_DECL(128)
+PMLP_FWD_S_DECL(256)
+#undef PMLP_FWD_S_DECL
+
+// Outputs per model as k_fwd_s sums them.
+inline int step_om(int32_t O) { return O <= 2 ? 2 : 4; }
+
 hipError_t launch_init_params(float* W1, int64_t N, int32_t F, int32_t F4, float bound1,
                               float* W2, int64_t ldw, int32_t O, const int32_t* mid,
                               const float* bound2, uint64_t key, hipStream_t s);
@@ -238,6 +295,9 @@ hipError_t launch_hidden_out(const float* Zt, int32_t Bp, int32_t B, int64_t N,
                              hipStream_t s, bool zb = false);
 
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t s);
+// info[n] = actn[n], + 256 at the last unit of a model (0 for n >= N)
+hipError_t launch_unit_info(const int32_t* mid, const int32_t* actn, int64_t N, int64_t Npad,
+                            int32_t* info, hipStream_t s);
 
 // dst[r ldd + c] = src[r lds + c] for r < rows, c < cols.
 hipError_t launch_copy_rows(float* dst, int64_t ldd, const float* src, int64_t lds, int64_t rows,

@@ -1,0 +1,130 @@
+"""The sample-split forward (k_fwd_s: product, activation and M3 forward in
+one kernel) against the fp64 oracle at the edges of its instances: every
+column-block count (F rounded to 4 a multiple of 16, of 32, and with 4, 8 and
+12 columns past it), every batch class (16 to 256 samples, full and ragged),
+two to four outputs, models narrower than a 16-unit tile and several in one
+tile, models that end on and off tile edges or take many stages, and packs of
+one to many groups per workgroup; the training step that continues from its Z
+and logits.  Bars as in the other parity tests (per-model normwise 1e-5)."""
+import zlib
+
+import numpy as np
+import pytest
+
+import pmlp_workloads as wl
+from parity import dw2_terms, err_cols, err_dw2, err_logits, err_losses, err_rows
+
+pytestmark = pytest.mark.gpu
+
+TOL_STEP = 1e-5
+EDGES = [3, 1, 1, 17, 16, 15, 70, 2, 1, 33, 65, 5, 48, 1, 16, 64]
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    torch.cuda.set_device(0)
+    return torch
+
+
+@pytest.fixture(scope="module")
+def pm(torch):
+    import paper_2206_08369_amd as pm
+    pm.load_library()
+    return pm
+
+
+@pytest.fixture(autouse=True)
+def default_path(monkeypatch):
+    monkeypatch.delenv("PMLP_GENERIC_KERNELS", raising=False)
+    monkeypatch.delenv("PMLP_FUSED_FORWARD", raising=False)
+
+
+def dev(torch, a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+# (F, O, B, models): at least 1,024 units where the batch is above 32
+SHAPES = [
+    (3, 2, 40, "mixed"), (12, 4, 64, "mixed"), (16, 3, 100, "mixed"), (30, 2, 128, "narrow"),
+    (33, 4, 200, "mixed"), (48, 2, 250, "mixed"), (64, 3, 64, "narrow"), (76, 2, 129, "mixed"),
+    (80, 4, 256, "narrow"), (96, 2, 100, "mixed"), (100, 2, 256, "mixed"), (104, 3, 130, "narrow"),
+    (100, 4, 33, "mixed"), (50, 2, 128, "narrow"), (100, 2, 250, "many"), (100, 2, 256, "wide"),
+    (104, 4, 16, "few"), (100, 2, 20, "few"), (9, 3, 1, "few"), (68, 2, 32, "mixed"),
+]
+
+
+def inputs(F, O, B, kind):
+    rng = np.random.default_rng(zlib.crc32(repr((F, O, B, kind)).encode()))
+    if kind == "mixed":       # widths on and off tile edges, and random models
+        hs = np.concatenate([EDGES, rng.integers(1, 71, 60)])
+    elif kind == "narrow":    # widths of 1 to 12: several models per tile
+        hs = rng.integers(1, 13, 900)
+    elif kind == "many":      # several groups per workgroup
+        hs = rng.integers(1, 60, 9000)
+    elif kind == "wide":      # models of many stages, one activation to a tile
+        hs = np.tile(np.arange(1, 401), 1)
+    else:
+        hs = np.array([1, 20, 3, 16, 7, 40, 1])
+    hs = hs.astype(np.int32)
+    acts = rng.integers(0, 10, len(hs)).astype(np.int32)
+    X, y = wl.make_dataset(F, O, B, seed=int(rng.integers(1 << 30)))
+    return hs, acts, X, y
+
+
+def sampled(hs, acts, W1, W2, kind):
+    """Models and units the oracle looks at (the models are independent)."""
+    step = {"many": 97, "wide": 13}.get(kind, 1)
+    off = np.concatenate([[0], np.cumsum(hs)])
+    models = np.arange(0, len(hs), step)
+    rows = np.concatenate([np.arange(off[m], off[m + 1]) for m in models])
+    return models, rows, hs[models], acts[models], W1[rows], W2[:, rows]
+
+
+@pytest.mark.parametrize("F,O,B,kind", SHAPES)
+def test_logits_and_hidden(pm, orc, torch, F, O, B, kind):
+    hs, acts, X, _ = inputs(F, O, B, kind)
+    net = pm.PackedMLP(F, O, hs, acts, seed=21)
+    W1, W2 = net.get_params()
+    models, rows, hs_s, ac_s, W1_s, W2_s = sampled(hs, acts, W1, W2, kind)
+    Xd = dev(torch, X)
+    got = net.forward(Xd).cpu().numpy()
+    assert net.kernel_variants()["fwd_m3"] == ("k_fwd_s", pm.PMLP_ARITH_X3)
+    assert err_logits(got[:, models], orc.forward(hs_s, ac_s, W1_s, W2_s, X)).max() <= TOL_STEP
+    Z, _ = net.hidden(Xd)
+    RZ, _ = orc.hidden(hs_s, ac_s, W1_s, X)
+    assert err_cols(Z.cpu().numpy()[:, rows], RZ, hs_s).max() <= TOL_STEP
+    net.close()
+
+
+@pytest.mark.parametrize("F,O,B", [(100, 2, 256), (36, 4, 140)])
+def test_step_from_its_forward(pm, orc, torch, F, O, B):
+    hs, acts, X, y = inputs(F, O, B, "wide")
+    net = pm.PackedMLP(F, O, hs, acts, seed=26)
+    W1, W2 = net.get_params()
+    models, rows, hs_s, ac_s, W1_s, W2_s = sampled(hs, acts, W1, W2, "wide")
+    dW1, dW2 = (t.cpu().numpy() for t in net.gradients(dev(torch, X), dev(torch, y)))
+    kv = net.kernel_variants()
+    assert kv["fwd_m3"][0] == "k_fwd_s" and kv["bwd_fused"][0] == "k_bwd_x3"
+    r1, r2, rl, allow = orc.gradients(hs_s, ac_s, W1_s, W2_s, X, y)
+    assert err_rows(dW1[rows], r1, hs_s, allow).max() <= TOL_STEP
+    terms = dw2_terms(orc, hs_s, ac_s, W1_s, W2_s, X, y)
+    assert err_dw2(dW2[:, rows], r2, hs_s, terms).max() <= TOL_STEP
+    assert err_losses(net.losses()[models], rl).max() <= TOL_STEP
+    net.close()
+
+
+@pytest.mark.parametrize("F,O,B", [(50, 2, 1000), (20, 3, 300), (100, 2, 513)])
+def test_forward_of_large_batches_equals_its_parts(pm, torch, F, O, B):
+    """A forward pass over more than 256 samples runs them in batches of one
+    class; the parts alone, in batches of another, sum each model's units in
+    another order only."""
+    hs, acts, X, _ = inputs(F, O, B, "mixed")
+    net = pm.PackedMLP(F, O, hs, acts, seed=24)
+    Xd = dev(torch, X)
+    whole = net.forward(Xd)
+    assert net.kernel_variants()["fwd_m3"][0] == "k_fwd_s"
+    parts = torch.cat([net.forward(Xd[s:s + 64]) for s in range(0, B, 64)])
+    assert err_logits(whole.cpu().numpy(), parts.cpu().numpy()).max() <= TOL_STEP
+    net.close()
