@@ -68,6 +68,7 @@ struct FwdShape {
 
 constexpr int kStepOne = 256, kStepEnd = 512;  // bits of a tile's word
 constexpr int kStepLast = 256;                 // bit of a unit's uinfo
+constexpr int kStepPad = 512;                  // of a tile's row past its group
 
 __host__ __device__ constexpr int fwd_tile_bytes(int NC, int rem, int OM) {
   return NC * 3072 + rem * 256 + 64 * (1 + OM) + 16;
@@ -270,7 +271,8 @@ void k_fwd_s(FwdSArgs a) {
     float w2[OM];
   };
   // row li of this wave's tile of the stage (tiles and rows past the group
-  // repeat its last unit with zero output weights and no end mark)
+  // repeat its last unit with zero output weights and no end mark; put() makes
+  // their strip zero, or a last unit that overflows would add 0 inf)
   auto fetch = [&](Raw& r, const Pos& p) {
     const int last = (p.len - 1) >> 4;
     const int t = p.s * ST + wave < last ? p.s * ST + wave : last;
@@ -297,13 +299,22 @@ void k_fwd_s(FwdSArgs a) {
     for (int q = 0; q < RM; ++q)
       r.t[q] = wt[wo + (uint32_t)(32 * NC + 4 * (q < rem ? q : 0) + lk)];
     const int info = (a.uinfo + p0)[row];
-    r.info = (in ? info : info & 255) | (((a.mid + p0)[row] - p.m0) << 10);
+    r.info = (in ? info : (info & 255) | kStepPad) | (((a.mid + p0)[row] - p.m0) << 10);
 #pragma unroll
     for (int o = 0; o < OM; ++o)
       r.w2[o] = in && o < a.O ? (a.W2 + ((int64_t)o * a.ldw + p0))[row] : 0.f;
   };
-  auto put = [&](const Raw& r, int buf) {
+  auto put = [&](Raw& r, int buf) {
     char* base = lds + (buf * ST + wave) * TB;
+    if (__any(r.info & kStepPad)) {
+      const bool pad = r.info & kStepPad;
+#pragma unroll
+      for (int c = 0; c < 2 * NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r.c[c][e] = pad ? 0.f : r.c[c][e];
+#pragma unroll
+      for (int q = 0; q < RM; ++q) r.t[q] = pad ? 0.f : r.t[q];
+    }
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       bf16x8 p0, p1, p2;

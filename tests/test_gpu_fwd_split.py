@@ -128,3 +128,19 @@ def test_forward_of_large_batches_equals_its_parts(pm, torch, F, O, B):
     parts = torch.cat([net.forward(Xd[s:s + 64]) for s in range(0, B, 64)])
     assert err_logits(whole.cpu().numpy(), parts.cpu().numpy()).max() <= TOL_STEP
     net.close()
+
+
+@pytest.mark.parametrize("F,O,B,kind", [(12, 2, 16, "few"), (100, 3, 128, "narrow"),
+                                        (33, 2, 200, "mixed")])
+def test_overflow_stays_infinite(pm, torch, F, O, B, kind):
+    """Pre-activations of finite operands that overflow to infinity, positive
+    output weights: every logit is infinite, also of the models whose last tile
+    has rows past them (those add nothing, not 0 times infinity)."""
+    hs, _, _, _ = inputs(F, O, B, kind)
+    net = pm.PackedMLP(F, O, hs, np.arange(len(hs), dtype=np.int32) % 2, seed=5)
+    n = int(hs.sum())
+    net.set_params(np.full((n, F), 3e38, np.float32), np.ones((O, n), np.float32))
+    got = net.forward(torch.full((B, F), 10.0, device="cuda"))
+    assert net.kernel_variants()["fwd_m3"][0] == "k_fwd_s"
+    assert bool((got == float("inf")).all())
+    net.close()
