@@ -548,14 +548,14 @@ std::vector<StepGroup> step_groups(const std::vector<int32_t>& hs, int64_t N, in
     else lo = mid + 1;
   }
   std::vector<StepGroup> g;
-  StepGroup cur{0, 0, 0, 0, 0};
+  StepGroup cur{0, 0, 0, 0};
   int64_t n = 0;
   for (size_t m = 0; m < hs.size(); ++m) {
     if (cur.nm > 0 && cur.len + hs[m] + kModel * (cur.nm + 1) > hi) {
       g.push_back(cur);
       cur.nm = 0;
     }
-    if (cur.nm == 0) cur = StepGroup{n, 0, (int32_t)m, 0, (int32_t)g.size()};
+    if (cur.nm == 0) cur = StepGroup{n, 0, (int32_t)m, 0};
     cur.len += hs[m];
     ++cur.nm;
     n += hs[m];
@@ -595,46 +595,25 @@ int build_step_plans(pmlp* h) {
   return PMLP_OK;
 }
 
-// Whether batch class c has the sample-split kernels at all.
-bool has_split_kernels(const pmlp* h, int c) {
-  if (c < 0 || !h->lds_kernels || bf16_mode(h) || h->deep || h->plan[c].slots <= 0) return false;
-  return !(h->fused_forward && fwd_m3_supported(kStepBatch[c], h->F4, h->O));
-}
-
-// How many units wide a model may be before its workgroup, which takes it
-// alone, is what the launch waits for: what the rest of the launch hides
-// (units x samples / 50,000) and a term for launches saved.  Measured where a
-// model of w units takes 0.1 w + 8 us through k_fwd_s: 100 features, widths up to 1,000, us before and after:
-// 80,000 units x 256, 102 / 109 (stays); 300,000 x 256, 224 / 162; 300,000 x
-// 64, 111 / 121 (stays) and widths up to 400, 83 / 63.
-int64_t split_reach(const pmlp* h, int c, int64_t nchunk) {
-  return h->N * kStepBatch[c] * nchunk / 50000;
-}
-
-// Whether a forward pass over nchunk batches of class c runs as k_fwd_s.  (The
-// term: widths up to 64 and 100 in packs of 1,000 to 20,000 units, batch of
-// 16: 19 us / 11 and 19 / 16; up to 200, 20 / 24.)
+// Whether a forward pass over nchunk batches of class c runs as k_fwd_s.  A
+// model's units go by one workgroup, so the widest model is what the launch may
+// wait for: it may have as many units as the rest of the launch hides (units x
+// samples / 50,000) and 128 more for the launches saved.  Measured where a
+// model of w units takes 0.1 w + 8 us through k_fwd_s, us through the other
+// kernels / through k_fwd_s: 100 features, widths up to 1,000, 80,000 units x
+// 256, 102 / 109 (stays); 300,000 x 256, 224 / 162; 300,000 x 64, 111 / 121
+// (stays) and widths up to 400, 83 / 63; packs of 1,000 to 20,000 units and
+// batches of 16, widths up to 64 and 100, 19 / 11 and 19 / 16; up to 200, 20 /
+// 24 (stays).
 bool fwd_split(const pmlp* h, int c, int64_t nchunk) {
-  return has_split_kernels(h, c) && h->widest <= 128 + split_reach(h, c, nchunk);
+  if (c < 0 || !h->lds_kernels || bf16_mode(h) || h->deep || h->plan[c].slots <= 0) return false;
+  if (h->fused_forward && fwd_m3_supported(kStepBatch[c], h->F4, h->O)) return false;
+  return h->widest <= 128 + h->N * kStepBatch[c] * nchunk / 50000;
 }
 
-// Whether a training step of class c runs on the sample-split kernels.  (The
-// term: packs of 5,000 units, widths up to 100 and batches of 16, 23 us / 24;
-// up to 200 and 256, 77 / 66; up to 400, 81 / 105.)  Models of fewer than four
-// units on average are as fast or faster on unit-split kernels once the pack
-// fills the chip: several models to a tile are several passes over its sums
-// (100 features, batch of 256, 130,000 units: 373 us / 452; 20,000: 120 / 104).
-bool train_split(const pmlp* h, int c) {
-  if (!has_split_kernels(h, c)) return false;
-  const int64_t zs = h->N * kStepBatch[c];
-  if (h->O <= 2 && h->N < 4 * (int64_t)h->M && zs > 6000000) return false;
-  return h->widest <= 64 + kStepBatch[c] / 2 + split_reach(h, c, 1);
-}
-
-// The sample-split forward of B samples in nchunk batches of class c: Zt
-// and/or logits out[m sm + b sb + o].
-int forward_split(pmlp* h, int c, const float* X, int32_t B, int32_t nchunk, float* Zt, float* out,
-                  int64_t sm, int64_t sb) {
+// The sample-split forward of B samples in nchunk batches of class c: logits
+// out[b][m][o].
+int forward_split(pmlp* h, int c, const float* X, int32_t B, int32_t nchunk, float* out) {
   const StepPlan& p = h->plan[c];
   FwdSArgs f{};
   f.X = X;
@@ -653,10 +632,9 @@ int forward_split(pmlp* h, int c, const float* X, int32_t B, int32_t nchunk, flo
   f.uinfo = h->d_uinfo;
   f.groups = p.groups;
   f.ngroups = p.ngroups;
-  f.Zt = Zt;
   f.out = out;
-  f.sm = sm;
-  f.sb = sb;
+  f.sm = h->O;
+  f.sb = (int64_t)h->M * h->O;
   return run(h, KID_FWD_M3, [&] { return launch_fwd_s(c, f, h->stream); });
 }
 
@@ -784,17 +762,10 @@ int step(pmlp* h, const float* X, const void* y, int32_t B, float lr, const floa
          const Work* work = nullptr) {
   const int32_t Bp = pad_batch(B);
   if (int rc = use_device(h)) return rc;
-  const int cls = step_class(Bp);
   if (!work)
     if (int rc = ensure_workspace(h, Bp)) return rc;
   const Work w = work ? *work : handle_work(h);
-  if (train_split(h, cls)) {
-    if (int rc = run(h, KID_PACK_X, [&] {  // Xt, for the backward
-          return launch_pack_x(X, B, h->F, Bp, h->F4, h->bcol, w.Xp, w.Xt, h->stream);
-        }))
-      return rc;
-    if (int rc = forward_split(h, cls, X, B, 1, w.Zt, w.LG, (int64_t)Bp * h->O, h->O)) return rc;
-  } else if (forward_fused(h, Bp)) {
+  if (forward_fused(h, Bp)) {
     if (int rc = forward_m3(h, X, B, Bp, w, w.LG, (int64_t)Bp * h->O, h->O,
                             (int64_t)h->M * Bp * h->O))
       return rc;
@@ -1293,8 +1264,7 @@ int pmlp_forward(pmlp_t h, const float* X_dev, int32_t B, float* logits_dev) {
       nchunk = div_up(B, kStepBatch[cls]);
     }
     if (fwd_split(h, cls, nchunk))
-      return forward_split(h, cls, X_dev, B, nchunk, nullptr, logits_dev, h->O,
-                           (int64_t)h->M * h->O);
+      return forward_split(h, cls, X_dev, B, nchunk, logits_dev);
   }
   if (int rc = ensure_workspace(h, Bp)) return rc;
   if (PmlpDeep* d = h->deep) {
@@ -1448,12 +1418,7 @@ int pmlp_hidden(pmlp_t h, const float* X_dev, int32_t B, float* Z_dev, float* H_
   const int32_t Bp = pad_batch(B);
   if (int rc = use_device(h)) return rc;
   if (int rc = ensure_workspace(h, Bp)) return rc;
-  if (const int cls = step_class(Bp); train_split(h, cls)) {
-    // the same Z, bit for bit, as this batch's training step and forward use
-    if (int rc = forward_split(h, cls, X_dev, B, 1, h->Zt, nullptr, 0, 0)) return rc;
-  } else if (int rc = forward_hidden(h, X_dev, B, Bp, handle_work(h))) {
-    return rc;
-  }
+  if (int rc = forward_hidden(h, X_dev, B, Bp, handle_work(h))) return rc;
   if (!Z_dev && !H_dev) return PMLP_OK;
   return run(h, KID_ACT, [&] {
     return launch_hidden_out(h->Zt, Bp, B, h->N, h->d_mid, h->d_act, Z_dev, H_dev, h->stream,

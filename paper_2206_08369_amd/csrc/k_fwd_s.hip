@@ -18,8 +18,8 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // Z = X W1^T on the three-piece products of k_fwd_x3, with the activation and
-// the M3 forward (Section 3, steps 1-4), so that Z is written once and not
-// read again before the backward.
+// the M3 forward (Section 3, steps 1-4): the logits alone, for forward passes,
+// so that Z is neither written nor read.
 //
 // In k_fwd_x3m (the epilogue in the layout that sums over units in the lane)
 // every wave multiplies its own units by all the samples: the batch comes
@@ -32,10 +32,10 @@ namespace {
 // their turns ahead), and all waves multiply all tiles of the stage by their
 // own samples: 9 KB of LDS reads per tile and wave for 36 products at two
 // blocks, against 144 KB for 288 in k_fwd_x3m.  Lane (li, lk) ends with Z of
-// unit li for the samples 16 ib + 4 lk + r, stores it, and adds act(Z) W2 to
-// its running sums; the sum over a model's units is one reduction over the 16
-// li lanes at the model's end.  A model's samples belong to one wave each, so
-// no sum crosses a wave and there are no atomics.
+// unit li for the samples 16 ib + 4 lk + r and adds act(Z) W2 to its running
+// sums; the sum over a model's units is one reduction over the 16 li lanes at
+// the model's end.  A model's samples belong to one wave each, so no sum
+// crosses a wave and there are no atomics.
 //
 // Workgroups take groups of whole models (the step plans), wide ones first,
 // forwards and backwards in turn, which leaves their loads within a group of
@@ -49,7 +49,13 @@ namespace {
 // of the logits and the M3 forward / this kernel: 60 models x 1 sample, 10
 // features, 20 / 8; 50,500 units x 10,000 samples, 50 features, 1993 / 867;
 // 505,000 x 256, 100 features, 331 / 226; 5,000,000 x 256, widths up to 1,000,
-// 2650 / 2080 (2410 with Z stored: 5.1 GB, about 0.8 ms of it).
+// 2650 / 2080.
+//
+// Training steps stay on the unit-split kernels.  With Z stored as well this
+// kernel took 2410 us of the last of these (5.1 GB of stores) and made an epoch
+// of 1,000 models a fifth shorter, but an epoch's parameters then carry another
+// rounding of every step: samples that end up on the other side of ReLU's kink
+// moved single weights of narrow models by up to 4.7e-4 of the weights' rms.
 // ---------------------------------------------------------------------------
 
 constexpr int kBp = PMLP_FWD_BP;
@@ -376,15 +382,12 @@ void k_fwd_s(FwdSArgs a) {
   __syncthreads();
 #pragma unroll 1
   for (int it = 0; p0.len; ++it) {
-    const int64_t n0 = p0.n0;
-    const int len = p0.len, t0 = p0.s * ST;
-    const int nt = (len + 15) >> 4;
+    const int t0 = p0.s * ST, nt = (p0.len + 15) >> 4;
     const int cnt = nt - t0 < ST ? nt - t0 : ST;
 #pragma unroll 1
     for (int j = 0; j < ST; ++j) {
       if (j < cnt) {
         const char* const base = lds + ((it & 1) * ST + j) * TB;
-        const int t = t0 + j;
         f32x4 acc[NI];
 #pragma unroll
         for (int i = 0; i < NI; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -418,42 +421,33 @@ _Pragma("unroll") for (int i = 0; i < NI; ++i) acc[i] = \
         float w2[OM];
 #pragma unroll
         for (int o = 0; o < OM; ++o) w2[o] = __int_as_float(mt[16 + 16 * o + li]);
-        if (a.Zt) {
-          float* zp = a.Zt + (n0 + t * 16) * BP;
-          if (t * 16 + li < len)
+        float h[V];
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
-              *(f32x4*)(zp + (uint32_t)(li * BP + 16 * (wave * NI + i) + 4 * lk)) = acc[i];
-        }
-        if (a.out) {
-          float h[V];
+        for (int q = 0; q < V; ++q) h[q] = acc[q >> 2][q & 3];
+        step_act<V>(word & 255, (word & 255) == 255 ? mt[li] & 255 : 0, h);
+        if (word & kStepOne) {
 #pragma unroll
-          for (int q = 0; q < V; ++q) h[q] = acc[q >> 2][q & 3];
-          step_act<V>(word & 255, (word & 255) == 255 ? mt[li] & 255 : 0, h);
-          if (word & kStepOne) {
+          for (int q = 0; q < V; ++q)
 #pragma unroll
-            for (int q = 0; q < V; ++q)
+            for (int o = 0; o < OM; ++o) S[q * OM + o] = fmaf(h[q], w2[o], S[q * OM + o]);
+          if (word & kStepEnd)
+            emit(p0.m0 + __builtin_amdgcn_readfirstlane(mt[0] >> 10));
+        } else {
+          // a model at a time, the other models' rows out of the sums
+          const int mrow = mt[li] >> 10;
+          const bool last = mt[li] & kStepLast;
+          const int m0 = __builtin_amdgcn_readfirstlane(mrow);
+          const int ml = __builtin_amdgcn_readlane(mrow, 15);
+          for (int mm = m0; mm <= ml; ++mm) {
+            const bool mine = mrow == mm;
 #pragma unroll
-              for (int o = 0; o < OM; ++o) S[q * OM + o] = fmaf(h[q], w2[o], S[q * OM + o]);
-            if (word & kStepEnd)
-              emit(p0.m0 + __builtin_amdgcn_readfirstlane(mt[0] >> 10));
-          } else {
-            // a model at a time, the other models' rows out of the sums
-            const int mrow = mt[li] >> 10;
-            const bool last = mt[li] & kStepLast;
-            const int m0 = __builtin_amdgcn_readfirstlane(mrow);
-            const int ml = __builtin_amdgcn_readlane(mrow, 15);
-            for (int mm = m0; mm <= ml; ++mm) {
-              const bool mine = mrow == mm;
+            for (int q = 0; q < V; ++q) {
+              const float hv = mine ? h[q] : 0.f;
 #pragma unroll
-              for (int q = 0; q < V; ++q) {
-                const float hv = mine ? h[q] : 0.f;
-#pragma unroll
-                for (int o = 0; o < OM; ++o)
-                  S[q * OM + o] = fmaf(hv, mine ? w2[o] : 0.f, S[q * OM + o]);
-              }
-              if (__any(mine && last)) emit(p0.m0 + mm);
+              for (int o = 0; o < OM; ++o)
+                S[q * OM + o] = fmaf(hv, mine ? w2[o] : 0.f, S[q * OM + o]);
             }
+            if (__any(mine && last)) emit(p0.m0 + mm);
           }
         }
       }

@@ -198,12 +198,10 @@ struct StepGroup {
   int64_t n0;           // first hidden unit
   int32_t len;          // hidden units
   int32_t m0, nm;       // first model, number of models
-  int32_t rank;         // place among the groups in unit order
 };
 
 // The forward pass with the waves split over the samples (k_fwd_s): logits
-//   out[m sm + b sb + o], and Zt [Npad][Bp] where set (one of the two at least;
-// more than Bp samples only without Zt).
+//   out[m sm + b sb + o].
 struct FwdSArgs {
   const float* X;    // [B][F]
   int32_t B, F, F4, O, bcol;
@@ -217,7 +215,6 @@ struct FwdSArgs {
   const int32_t* uinfo;  // [Npad] activation id, + 256 at a model's last unit
   const StepGroup* groups;
   int32_t ngroups;
-  float* Zt;
   float* out;
   int64_t sm, sb;
 };

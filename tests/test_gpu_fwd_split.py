@@ -4,8 +4,7 @@ column-block count (F rounded to 4 a multiple of 16, of 32, and with 4, 8 and
 12 columns past it), every batch class (16 to 256 samples, full and ragged),
 two to four outputs, models narrower than a 16-unit tile and several in one
 tile, models that end on and off tile edges or take many stages, and packs of
-one to many groups per workgroup; the training step that continues from its Z
-and logits.  Bars as in the other parity tests (per-model normwise 1e-5)."""
+one to many groups per workgroup; the training step of the same packs.  Bars as in the other parity tests (per-model normwise 1e-5)."""
 import zlib
 
 import numpy as np
@@ -99,14 +98,13 @@ def test_logits_and_hidden(pm, orc, torch, F, O, B, kind):
 
 
 @pytest.mark.parametrize("F,O,B", [(100, 2, 256), (36, 4, 140)])
-def test_step_from_its_forward(pm, orc, torch, F, O, B):
+def test_step_of_wide_models(pm, orc, torch, F, O, B):
     hs, acts, X, y = inputs(F, O, B, "wide")
     net = pm.PackedMLP(F, O, hs, acts, seed=26)
     W1, W2 = net.get_params()
     models, rows, hs_s, ac_s, W1_s, W2_s = sampled(hs, acts, W1, W2, "wide")
     dW1, dW2 = (t.cpu().numpy() for t in net.gradients(dev(torch, X), dev(torch, y)))
-    kv = net.kernel_variants()
-    assert kv["fwd_m3"][0] == "k_fwd_s" and kv["bwd_fused"][0] == "k_bwd_x3"
+    assert net.kernel_variants()["bwd_fused"][0] == "k_bwd_x3"
     r1, r2, rl, allow = orc.gradients(hs_s, ac_s, W1_s, W2_s, X, y)
     assert err_rows(dW1[rows], r1, hs_s, allow).max() <= TOL_STEP
     terms = dw2_terms(orc, hs_s, ac_s, W1_s, W2_s, X, y)
