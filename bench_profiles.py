@@ -59,7 +59,7 @@ ROLE = {
     "k_fwd_lds_ring": "gemm_fwd", "k_fwd_x3": "gemm_fwd", "k_fwd_x3m": "fwd_m3",
     "k_fwd_s": "fwd_m3",
     "k_m3_fwd": "m3_fwd",
-    "k_m3_fwd_mf": "m3_fwd", "k_ce": "ce", "k_mse": "ce", "k_fill": "aux",
+    "k_m3_fwd_mf": "m3_fwd", "k_ce": "ce", "k_mse": "ce",
     "k_bwd_lds": "bwd_fused", "k_bwd_x3": "bwd_fused", "k_bwd_mf": "bwd_fused",
     "k_m3_bwd": "m3_bwd", "k_w1_to_bf16": "aux",
 }

@@ -638,13 +638,17 @@ int forward_split(pmlp* h, int c, const float* X, int32_t B, int32_t nchunk, flo
   return run(h, KID_FWD_M3, [&] { return launch_fwd_s(c, f, h->stream); });
 }
 
-// Batch copy and the input-to-hidden product (Section 3, step 1).
-int forward_hidden(pmlp* h, const float* X, int32_t B, int32_t Bp, const Work& w) {
+// Batch copy and the input-to-hidden product (Section 3, step 1).  Where the
+// halves of a wide segment will add their logits atomically, the batch copy
+// also clears those (the ncl floats from `clear`): a launch of their own took
+// 4.7 to 6.6 us of every step.
+int forward_hidden(pmlp* h, const float* X, int32_t B, int32_t Bp, const Work& w,
+                   float* clear = nullptr, int64_t ncl = 0) {
   if (bf16_mode(h)) {
     if (int rc = ensure_workspace_bf16(h, Bp)) return rc;
     if (int rc = ensure_w1b(h)) return rc;
     if (int rc = run(h, KID_PACK_X, [&] {
-          return launch_pack_x_bf16(X, B, h->F, Bp, h->F4, h->bcol, h->Xp16, h->Xt16,
+          return launch_pack_x_bf16(X, B, h->F, Bp, h->F4, h->bcol, h->Xp16, h->Xt16, clear, ncl,
                                     h->stream);
         }))
       return rc;
@@ -667,7 +671,7 @@ int forward_hidden(pmlp* h, const float* X, int32_t B, int32_t Bp, const Work& w
     return run(h, KID_GEMM_FWD, [&] { return launch_gemm_bf16(g, EPI_STORE, h->stream); });
   }
   if (int rc = run(h, KID_PACK_X, [&] {
-        return launch_pack_x(X, B, h->F, Bp, h->F4, h->bcol, w.Xp, w.Xt, h->stream);
+        return launch_pack_x(X, B, h->F, Bp, h->F4, h->bcol, w.Xp, w.Xt, clear, ncl, h->stream);
       }))
     return rc;
   if (h->lds_kernels && fwd_lds_supported(Bp, h->F4)) {
@@ -723,12 +727,10 @@ bool forward_fused(const pmlp* h, int32_t Bp) {
 int forward_m3(pmlp* h, const float* X, int32_t B, int32_t Bp, const Work& w, float* out,
                int64_t sm, int64_t sb, int64_t nout) {
   if (int rc = run(h, KID_PACK_X, [&] {
-        return launch_pack_x(X, B, h->F, Bp, h->F4, h->bcol, w.Xp, w.Xt, h->stream);
+        return launch_pack_x(X, B, h->F, Bp, h->F4, h->bcol, w.Xp, w.Xt, out,
+                             h->has_split ? nout : 0, h->stream);
       }))
     return rc;
-  if (h->has_split) {
-    if (int rc = run(h, KID_AUX, [&] { return launch_fill(out, nout, 0.f, h->stream); })) return rc;
-  }
   FwdM3Args f{};
   f.W1 = h->W1;
   f.Xp = w.Xp;
@@ -770,13 +772,9 @@ int step(pmlp* h, const float* X, const void* y, int32_t B, float lr, const floa
                             (int64_t)h->M * Bp * h->O))
       return rc;
   } else {
-    if (int rc = forward_hidden(h, X, B, Bp, w)) return rc;
-    if (h->has_split) {
-      if (int rc = run(h, KID_AUX, [&] {
-            return launch_fill(w.LG, (int64_t)h->M * Bp * h->O, 0.f, h->stream);
-          }))
-        return rc;
-    }
+    if (int rc = forward_hidden(h, X, B, Bp, w, w.LG,
+                                h->has_split ? (int64_t)h->M * Bp * h->O : 0))
+      return rc;
     if (int rc = run(h, KID_M3_FWD, [&] {
           return launch_m3_fwd(w.Zt, Bp, B, h->W2, h->Npad, h->O, h->d_seg_off, h->d_act,
                                h->d_tiles, h->d_order, h->ntiles, h->b2, w.LG, (int64_t)Bp * h->O,
@@ -939,9 +937,10 @@ DeepArgs deep_args(const pmlp* h) {
 // Forward of a pack with two hidden layers up to the second layer's
 // pre-activations: Z1 = X W1^T (the one-layer product), then per model
 // Z2 = W12 act(Z1) (Section 7, Figure 3).
-int forward_deep(pmlp* h, const float* X, int32_t B, int32_t Bp, const Work& w) {
+int forward_deep(pmlp* h, const float* X, int32_t B, int32_t Bp, const Work& w,
+                 float* clear, int64_t ncl) {
   PmlpDeep* d = h->deep;
-  if (int rc = forward_hidden(h, X, B, Bp, w)) return rc;
+  if (int rc = forward_hidden(h, X, B, Bp, w, clear, ncl)) return rc;
   const DeepArgs a = deep_args(h);
   return run(h, KID_DEEP, [&] {
     return launch_seg_fwd(w.Zt, d->Zt2, Bp, a, d->d_ufwd, d->nufwd, h->stream);
@@ -958,13 +957,9 @@ int step_deep(pmlp* h, const float* X, const int32_t* y, int32_t B, float lr, fl
   if (int rc = ensure_workspace(h, Bp)) return rc;
   if (int rc = ensure_deep_workspace(h, Bp)) return rc;
   const Work w = handle_work(h);
-  if (int rc = forward_deep(h, X, B, Bp, w)) return rc;
-  if (d->has_split2) {
-    if (int rc = run(h, KID_AUX, [&] {
-          return launch_fill(w.LG, (int64_t)h->M * Bp * h->O, 0.f, h->stream);
-        }))
-      return rc;
-  }
+  if (int rc = forward_deep(h, X, B, Bp, w, w.LG,
+                            d->has_split2 ? (int64_t)h->M * Bp * h->O : 0))
+    return rc;
   if (int rc = run(h, KID_M3_FWD, [&] {
         return launch_m3_fwd(d->Zt2, Bp, B, h->W2, d->N2pad, h->O, d->d_off2, h->d_act,
                              d->d_tiles2, d->d_order2, d->ntiles2, nullptr, w.LG,
@@ -1269,13 +1264,9 @@ int pmlp_forward(pmlp_t h, const float* X_dev, int32_t B, float* logits_dev) {
   if (int rc = ensure_workspace(h, Bp)) return rc;
   if (PmlpDeep* d = h->deep) {
     if (int rc = ensure_deep_workspace(h, Bp)) return rc;
-    if (int rc = forward_deep(h, X_dev, B, Bp, handle_work(h))) return rc;
-    if (d->has_split2) {
-      if (int rc = run(h, KID_AUX, [&] {
-            return launch_fill(logits_dev, (int64_t)B * h->M * h->O, 0.f, h->stream);
-          }))
-        return rc;
-    }
+    if (int rc = forward_deep(h, X_dev, B, Bp, handle_work(h), logits_dev,
+                              d->has_split2 ? (int64_t)B * h->M * h->O : 0))
+      return rc;
     return run(h, KID_M3_FWD, [&] {
       return launch_m3_fwd(d->Zt2, Bp, B, h->W2, d->N2pad, h->O, d->d_off2, h->d_act, d->d_tiles2,
                            d->d_order2, d->ntiles2, nullptr, logits_dev, h->O,
@@ -1285,13 +1276,9 @@ int pmlp_forward(pmlp_t h, const float* X_dev, int32_t B, float* logits_dev) {
   if (forward_fused(h, Bp))
     return forward_m3(h, X_dev, B, Bp, handle_work(h), logits_dev, h->O, (int64_t)h->M * h->O,
                       (int64_t)B * h->M * h->O);
-  if (int rc = forward_hidden(h, X_dev, B, Bp, handle_work(h))) return rc;
-  if (h->has_split) {
-    if (int rc = run(h, KID_AUX, [&] {
-          return launch_fill(logits_dev, (int64_t)B * h->M * h->O, 0.f, h->stream);
-        }))
-      return rc;
-  }
+  if (int rc = forward_hidden(h, X_dev, B, Bp, handle_work(h), logits_dev,
+                              h->has_split ? (int64_t)B * h->M * h->O : 0))
+    return rc;
   return run(h, KID_M3_FWD, [&] {
     return launch_m3_fwd(h->Zt, Bp, B, h->W2, h->Npad, h->O, h->d_seg_off, h->d_act, h->d_tiles,
                          h->d_order, h->ntiles, h->b2, logits_dev, h->O, (int64_t)h->M * h->O,

@@ -242,9 +242,11 @@ hipError_t launch_init_biases(float* W1, int64_t N, int32_t F4, int32_t bcol, fl
                               uint64_t key, hipStream_t s);
 
 // Column bcol (>= F, or -1 for none) of the copies is 1 for the B real
-// samples: the constant input whose weight is the hidden bias.
+// samples: the constant input whose weight is the hidden bias.  Both packs also
+// clear the ncl floats from `clear` (logits the M3 forward adds halves to).
 hipError_t launch_pack_x(const float* X, int32_t B, int32_t F, int32_t Bp, int32_t F4,
-                         int32_t bcol, float* Xp, float* Xt, hipStream_t s);
+                         int32_t bcol, float* Xp, float* Xt, float* clear, int64_t ncl,
+                         hipStream_t s);
 
 // bf16 copies of the batch (round to nearest even), zero padded:
 //   Xp16 [Bp][bf16_ld(F4)]  (operand of Z = X W1^T)
@@ -255,7 +257,7 @@ hipError_t launch_w1_to_bf16(const float* W1, int64_t Npad, int32_t F4, unsigned
 
 hipError_t launch_pack_x_bf16(const float* X, int32_t B, int32_t F, int32_t Bp, int32_t F4,
                               int32_t bcol, unsigned short* Xp16, unsigned short* Xt16,
-                              hipStream_t s);
+                              float* clear, int64_t ncl, hipStream_t s);
 
 // order: tile indices in launch order (widest first).
 hipError_t launch_m3_fwd(const float* Zt, int32_t Bp, int32_t B, const float* W2, int64_t ldw,
@@ -291,7 +293,6 @@ hipError_t launch_hidden_out(const float* Zt, int32_t Bp, int32_t B, int64_t N,
                              const int32_t* mid, const int32_t* act, float* Z, float* H,
                              hipStream_t s, bool zb = false);
 
-hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t s);
 // info[n] = actn[n], + 256 at the last unit of a model (0 for n >= N)
 hipError_t launch_unit_info(const int32_t* mid, const int32_t* actn, int64_t N, int64_t Npad,
                             int32_t* info, hipStream_t s);

@@ -4,7 +4,8 @@ column-block count (F rounded to 4 a multiple of 16, of 32, and with 4, 8 and
 12 columns past it), every batch class (16 to 256 samples, full and ragged),
 two to four outputs, models narrower than a 16-unit tile and several in one
 tile, models that end on and off tile edges or take many stages, and packs of
-one to many groups per workgroup; the training step of the same packs.  Bars as in the other parity tests (per-model normwise 1e-5)."""
+one to many groups per workgroup; the training step of the same packs, whose
+logits are cleared by its batch copy.  Bars as in the other parity tests (per-model normwise 1e-5)."""
 import zlib
 
 import numpy as np
