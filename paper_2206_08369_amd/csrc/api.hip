@@ -1053,6 +1053,12 @@ void build_tiles(const std::vector<int32_t>& hs, int64_t cap, std::vector<Tile3>
                  bool& has_split) {
   tiles.clear();
   has_split = false;
+  // A pack of few models at the smallest cap has waves to spare and its launch
+  // lasts as long as its longest tile, a chain of a few trips to memory per
+  // model: one model a tile, with the same sums (60 models of 1..10 units, an
+  // epoch of 32 steps: 986 -> 757 us).  (At most kTile3Count tiles:
+  // 2^20 samples of them are 2^31 threads, a grid's limit is 2^32.)
+  const bool alone = cap == kTile3Min && 2 * (int64_t)hs.size() <= kTile3Count;
   Tile3 cur{0, 0, 0, 0, 0};
   int64_t n = 0;
   for (size_t m = 0; m < hs.size(); ++m) {
@@ -1065,7 +1071,7 @@ void build_tiles(const std::vector<int32_t>& hs, int64_t cap, std::vector<Tile3>
       tiles.push_back(Tile3{n + half, (int32_t)(w - half), (int32_t)m, 1, 0});
       has_split = true;
     } else {
-      if (cur.len > 0 && cur.len + w > cap) {
+      if (cur.len > 0 && (alone || cur.len + w > cap)) {
         tiles.push_back(cur);
         cur.len = 0;
       }
