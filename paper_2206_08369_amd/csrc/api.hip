@@ -630,6 +630,7 @@ int forward_split(pmlp* h, int c, const float* X, int32_t B, int32_t nchunk, flo
   f.b2 = h->b2;
   f.mid = h->d_mid;
   f.uinfo = h->d_uinfo;
+  f.seg_off = h->d_seg_off;
   f.groups = p.groups;
   f.ngroups = p.ngroups;
   f.out = out;

@@ -51,6 +51,21 @@ namespace {
 // 505,000 x 256, 100 features, 331 / 226; 5,000,000 x 256, widths up to 1,000,
 // 2650 / 2080.
 //
+// The six products hold an fp32 product as long as no piece and no partial sum
+// leaves the range of fp32.  An infinite operand has NaN for its second piece,
+// one above the largest bf16 (3.39e38) an infinite first one, and where a sum
+// overflows, the lower products, added first, may do so with the other sign
+// (1300 x 3e38 is inf - inf).  All of these end in NaN, which every activation
+// here passes on, so the logits say where it happened: a wave that wrote a NaN
+// computes those models again at its end with fp32 products, whose result
+// (finite, infinite or NaN, as fp32 sums are) replaces the NaN.  A test of each
+// tile's operands instead made the launch 3 to 6 % longer; this, a comparison per
+// logit, 0 to 2 %.
+// For finite operands the pieces lose nothing: norm of the error of the logits
+// over their norm against 64 bits, fp32 MFMAs / this kernel: 16 features 1.2e-7 /
+// 0.9e-7, 100 features and 16 or 64 samples 1.9e-7 / 1.5e-7 (120 models of 1 to
+// 100 units).  (A piece of an operand below 1e-33 is subnormal.)
+//
 // Training steps stay on the unit-split kernels.  With Z stored as well this
 // kernel took 2410 us of the last of these (5.1 GB of stores) and made an epoch
 // of 1,000 models a fifth shorter, but an epoch's parameters then carry another
@@ -83,6 +98,12 @@ __host__ __device__ constexpr int fwd_tile_bytes(int NC, int rem, int OM) {
 template <class T>
 __device__ __forceinline__ T step_opaque(T v) {
   asm volatile("" : "+v"(v));
+  return v;
+}
+
+template <class T>
+__device__ __forceinline__ T step_opaque_s(T v) {
+  asm volatile("" : "+s"(v));
   return v;
 }
 
@@ -161,7 +182,15 @@ __device__ __forceinline__ void step_reduce(float* v, int li) {
   PMLP_ACT(0) PMLP_ACT(1) PMLP_ACT(2) PMLP_ACT(3) PMLP_ACT(4) PMLP_ACT(5) PMLP_ACT(6)       \
   PMLP_ACT(7) PMLP_ACT(8) PMLP_ACT(9) PMLP_ACT(10) PMLP_ACT(11) PMLP_ACT(12)
 
-template <int NV>
+// act_fwd, with KEEP NaN for NaN also where its choice of a branch drops it.
+template <bool KEEP>
+__device__ __forceinline__ float step_act_fwd(int a, float z) {
+  if (KEEP && a == 1) return z <= 0.f ? 0.f : z;
+  if (KEEP && a == 11) return fabsf(z) <= 0.5f ? 0.f : z;
+  return act_fwd(a, z);
+}
+
+template <bool KEEP, int NV>
 __device__ __forceinline__ void step_act(int act, int arow, float (&z)[NV]) {
   const bool one = act < 255;
   int A = one ? act : __builtin_amdgcn_readfirstlane(arow);
@@ -175,7 +204,7 @@ __device__ __forceinline__ void step_act(int act, int arow, float (&z)[NV]) {
     switch (A) {
 #define PMLP_ACT(AA)                                                         \
   case AA: {                                                                 \
-    _Pragma("unroll") for (int j = 0; j < NV; ++j) v[j] = act_fwd(AA, z[j]); \
+    _Pragma("unroll") for (int j = 0; j < NV; ++j) v[j] = step_act_fwd<KEEP>(AA, z[j]); \
     break;                                                                   \
   }
       PMLP_STEP_ACTS
@@ -196,6 +225,66 @@ __device__ __forceinline__ void step_act(int act, int arow, float (&z)[NV]) {
   }
 }
 
+// The logits of model m for the samples b0 .. b0+15 again, where one of them is
+// NaN: the products as fp32 MFMAs, 16 columns a step (4 lk .. 4 lk + 3 of them
+// each lane's).
+constexpr int kRedo = 4;  // steps whose loads are in flight
+template <int OM>
+__device__ __forceinline__ void step_model_fp32(const FwdSArgs& a, int m, int b0, int li, int lk) {
+  // value `idx` of a lane's 4 OM sums after the reduction over the 16 li
+  const int idx = OM == 2 ? li >> 1 : li, o1 = idx % OM, b1 = b0 + 4 * lk + idx / OM;
+  float* const dst = a.out + (int64_t)m * a.sm + (int64_t)b1 * a.sb + o1;
+  const bool mine = b1 < a.B && o1 < a.O;
+  const float old = mine ? *dst : 0.f;
+  if (!__any(old != old)) return;
+  const int b = b0 + li, bc = b < a.B ? b : a.B - 1;
+  const float* const xr = a.X + (int64_t)bc * a.F;
+  const int64_t u1 = a.seg_off[m + 1];
+  const int act = a.uinfo[a.seg_off[m]] & 255;
+  float S[4 * OM];
+#pragma unroll
+  for (int q = 0; q < 4 * OM; ++q) S[q] = 0.f;
+#pragma unroll 1
+  for (int64_t u0 = a.seg_off[m]; u0 < u1; u0 += 16) {
+    const bool in = u0 + li < u1;
+    const int64_t u = in ? u0 + li : u1 - 1;
+    const float* const wr = a.W1 + u * a.F4;
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int k0 = 4 * lk; k0 - 4 * lk < a.F4; k0 += 16 * kRedo) {
+      f32x4 wv[kRedo], xv[kRedo];
+#pragma unroll
+      for (int j = 0; j < kRedo; ++j) {
+        const int k = k0 + 16 * j;
+        wv[j] = *(const f32x4*)(wr + (k < a.F4 ? k : 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) xv[j][e] = xr[k + e < a.F ? k + e : 0];
+      }
+#pragma unroll
+      for (int j = 0; j < kRedo; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = k0 + 16 * j + e;
+          const float x = k < a.F ? xv[j][e] : (k == a.bcol ? 1.f : 0.f);
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, k < a.F4 ? wv[j][e] : 0.f, acc, 0, 0, 0);
+        }
+    }
+    float h[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h[r] = in ? acc[r] : 0.f;
+    step_act<false>(act, 0, h);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h[r] = in ? h[r] : 0.f;
+#pragma unroll
+    for (int o = 0; o < OM; ++o) {
+      const float w2 = a.W2[(int64_t)(o < a.O ? o : 0) * a.ldw + u];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) S[r * OM + o] = fmaf(h[r], in ? w2 : 0.f, S[r * OM + o]);
+    }
+  }
+  step_reduce<4 * OM, 8>(S, li);
+  if (mine && !(OM == 2 && (li & 1))) *dst = S[0] + (a.b2 ? a.b2[(int64_t)m * a.O + o1] : 0.f);
+}
 
 template <int TQ, int OM>
 __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2)))
@@ -349,6 +438,7 @@ void k_fwd_s(FwdSArgs a) {
   float S[V * OM];  // running sums of the open model
 #pragma unroll
   for (int q = 0; q < V * OM; ++q) S[q] = 0.f;
+  uint64_t bad = 0;  // bit m % 64: a logit of model m is NaN
   // the open model ends: its logits, and the sums start again
   auto emit = [&](int mm) {
     step_reduce<V * OM, 8>(S, li);
@@ -361,6 +451,7 @@ void k_fwd_s(FwdSArgs a) {
       const int b = 16 * (wave * NI + (q >> 2)) + 4 * lk + (q & 3);
       float s = S[e];
       if (a.b2 && o < a.O) s += a.b2[(int64_t)mm * a.O + o];
+      if (NC) bad |= (uint64_t)(__any(s != s) ? 1 : 0) << (mm & 63);
       if (V * OM < 16 && (li & 1)) continue;
       if (b < B && o < a.O) dst[b * a.sb + o] = s;
     }
@@ -424,7 +515,7 @@ _Pragma("unroll") for (int i = 0; i < NI; ++i) acc[i] = \
         float h[V];
 #pragma unroll
         for (int q = 0; q < V; ++q) h[q] = acc[q >> 2][q & 3];
-        step_act<V>(word & 255, (word & 255) == 255 ? mt[li] & 255 : 0, h);
+        step_act<NC != 0>(word & 255, (word & 255) == 255 ? mt[li] & 255 : 0, h);
         if (word & kStepOne) {
 #pragma unroll
           for (int q = 0; q < V; ++q)
@@ -461,6 +552,27 @@ _Pragma("unroll") for (int i = 0; i < NI; ++i) acc[i] = \
     p1 = p2;
     p2 = next(p2);
     __syncthreads();
+  }
+  if (NC && bad) {
+    __threadfence_block();  // (a logit is read by another lane than wrote it)
+    // (arguments and indices afresh: held over the stages they would cost
+    // registers there)
+    const FwdSArgs& r = *(const FwdSArgs*)step_opaque_s(__builtin_amdgcn_kernarg_segment_ptr());
+    const int t = step_opaque((int)threadIdx.x), bid = step_opaque_s((int)blockIdx.x);
+    const int c = bid / r.wpc, first = bid - c * r.wpc;
+    const int b0 = c * BP + 16 * NI * __builtin_amdgcn_readfirstlane(t >> 6);
+#pragma unroll 1
+    for (int k = 0;; ++k) {
+      const int g = k * r.wpc + (k & 1 ? r.wpc - 1 - first : first);
+      if (g >= r.ngroups) break;
+      const StepGroup q = r.groups[g];
+#pragma unroll 1
+      for (int m = q.m0; m < q.m0 + q.nm; ++m)
+        if (bad >> (m & 63) & 1)
+#pragma unroll 1
+          for (int i = 0; i < NI; ++i)
+            step_model_fp32<OM>(r, m, b0 + 16 * i, t & 15, (t & 63) >> 4);
+    }
   }
 }
 

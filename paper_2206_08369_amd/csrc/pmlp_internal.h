@@ -213,6 +213,7 @@ struct FwdSArgs {
   const float* b2;   // [M][O] or null
   const int32_t* mid;    // [Npad] model of each unit
   const int32_t* uinfo;  // [Npad] activation id, + 256 at a model's last unit
+  const int64_t* seg_off;  // [M+1] first unit of each model
   const StepGroup* groups;
   int32_t ngroups;
   float* out;

@@ -143,3 +143,74 @@ def test_overflow_stays_infinite(pm, torch, F, O, B, kind):
     assert net.kernel_variants()["fwd_m3"][0] == "k_fwd_s"
     assert bool((got == float("inf")).all())
     net.close()
+
+
+# products of one column whose fp32 value a sum of bf16 pieces loses: pieces
+# that overflow with the other sign, an operand above the largest bf16,
+# infinite operands, and ordinary values between them
+WILD = [(1.1e20, 1.1e21), (1300.0, 3e38), (1.3e20, -1.7e25), (1.0000001, 3.4e38),
+        (20.07, 3e38), (float("inf"), -2.0), (0.5, float("inf")), (-3e38, 0.25), (0.37, 1.3),
+        (float("nan"), 0.7)]
+
+
+def saturated(z):
+    with np.errstate(over="ignore"):
+        return z.astype(np.float32).astype(np.float64)
+
+
+@pytest.mark.parametrize("F,O,B,biases", [
+    (40, 2, 16, False), (100, 4, 30, True), (64, 2, 64, False), (50, 2, 128, False),
+    (33, 3, 200, True), (16, 2, 256, False), (100, 2, 250, False), (70, 4, 300, False),
+    (50, 2, 1000, True), (99, 2, 380, False)])
+def test_values_out_of_the_pieces_range(pm, torch, F, O, B, biases):
+    """Each logit is finite, infinite or NaN as the fp32 products of its sample
+    and weights are, and right where it is finite: large and infinite entries
+    in some samples and some models, on ordinary ones beside them."""
+    rng = np.random.default_rng(F * B)
+    hs, _, _, _ = inputs(F, O, B, "mixed")
+    n = int(hs.sum())
+    acts = np.resize([0, 1, 2, 3], len(hs)).astype(np.int32)
+    mid = np.repeat(np.arange(len(hs)), hs)
+    W1 = (rng.uniform(0.1, 1.0, (n, F)) * np.where(mid % 8 < 4, 1, -1)[:, None]).astype(np.float32)
+    W2 = rng.uniform(0.1, 1.0, (O, n)).astype(np.float32)
+    col = F // 2 if F < 64 else 3                  # within the first 32 columns
+    X = np.zeros((B, F), np.float32)
+    X[::3] = rng.standard_normal((len(X[::3]), F))  # ordinary samples
+    for b in range(B):
+        if b % 3:
+            X[b, col] = WILD[b % len(WILD)][0]
+    for m in range(0, len(hs), 7):                  # one model in seven
+        W1[mid == m] = 0.0
+        W1[mid == m, col] = WILD[(m // 7) % len(WILD)][1]
+    net = pm.PackedMLP(F, O, hs, acts, seed=2, biases=biases)
+    net.set_params(W1, W2)
+    b1, b2 = np.zeros(n, np.float32), np.zeros((len(hs), O), np.float32)
+    if biases:
+        b1 = rng.standard_normal(n).astype(np.float32)
+        b2 = rng.standard_normal(b2.shape).astype(np.float32)
+        net.set_biases(b1, b2)
+    got = net.forward(dev(torch, X)).cpu().numpy().astype(np.float64)
+    assert net.kernel_variants()["fwd_m3"][0] == "k_fwd_s"
+    net.close()
+    with np.errstate(all="ignore"):
+        A, C = X.astype(np.float64), W1.T.astype(np.float64)
+        Z, T = np.zeros((B, n)), np.zeros((B, n))
+        for f in range(F):                          # (as written: 0 times infinity is NaN)
+            Z += A[:, f:f + 1] * C[f]
+            T += np.abs(A[:, f:f + 1] * C[f])
+        Z = saturated(Z + b1)
+        a = acts[mid]
+        H = np.where(a == 0, Z, np.where(a == 1, np.where(Z > 0, Z, 0.0),
+                     np.where(a == 2, np.tanh(Z), 1.0 / (1.0 + np.exp(-Z)))))
+        # the size of what a logit sums: an error of Z enters with slope at most 1
+        size = np.where(np.isfinite(T), T, 0.0) + np.abs(b1) + np.abs(H)
+        off = np.concatenate([[0], np.cumsum(hs)])[:-1]
+        for o in range(O):
+            want = saturated(np.add.reduceat(H * W2[o], off, axis=1) + b2[:, o])
+            scale = np.add.reduceat(size * W2[o], off, axis=1) + np.abs(b2[:, o])
+            g = got[:, :, o]
+            assert np.array_equal(np.isnan(g), np.isnan(want))
+            assert np.array_equal(g[np.isinf(g)], want[np.isinf(g)])
+            ok = np.isfinite(want) & np.isfinite(g)
+            assert np.array_equal(ok, np.isfinite(want))
+            assert (np.abs(g - want)[ok] <= TOL_STEP * scale[ok]).all()
