@@ -178,14 +178,16 @@ bool bwd_lds_supported(int32_t Bp, int32_t F4, int32_t O);
 hipError_t launch_bwd_lds(const BwdArgs& a, hipStream_t s);
 
 // Workgroups of a kernel the current device holds at once; 0 if its dynamic
-// LDS does not fit (and the kernel then allows that much).
+// LDS does not fit.  The kernel is then allowed as much as the device has: the
+// limit belongs to the kernel, and a limit of `lds` would be lowered by a later
+// handle of another shape under the launches of an earlier one.
 inline int resident_blocks(const void* fn, int threads, size_t lds) {
   int dev = 0, cus = 0, lmax = 0, per = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       hipDeviceGetAttribute(&lmax, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
       lds > (size_t)lmax ||
-      hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+      hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lmax) != hipSuccess ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, threads, lds) != hipSuccess) {
     (void)hipGetLastError();
     return 0;

@@ -214,3 +214,21 @@ def test_values_out_of_the_pieces_range(pm, torch, F, O, B, biases):
             ok = np.isfinite(want) & np.isfinite(g)
             assert np.array_equal(ok, np.isfinite(want))
             assert (np.abs(g - want)[ok] <= TOL_STEP * scale[ok]).all()
+
+
+def test_handles_of_one_kernel_and_two_shapes(pm, orc, torch):
+    """Two live handles whose forward passes are the same kernel with different
+    amounts of LDS (159 KB for 108 columns, 151 KB for 100): the later and
+    smaller one leaves the earlier one its own."""
+    nets = []
+    for F in (108, 100):
+        hs, acts, X, _ = inputs(F, 2, 256, "mixed")
+        nets.append((pm.PackedMLP(F, 2, hs, acts, seed=F), hs, acts, X))
+    for _ in range(2):
+        for net, hs, acts, X in nets:
+            got = net.forward(dev(torch, X)).cpu().numpy()
+            assert net.kernel_variants()["fwd_m3"][0] == "k_fwd_s"
+            W1, W2 = net.get_params()
+            assert err_logits(got, orc.forward(hs, acts, W1, W2, X)).max() <= TOL_STEP
+    for net, *_ in nets:
+        net.close()
