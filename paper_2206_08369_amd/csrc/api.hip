@@ -98,11 +98,12 @@ struct PmlpDeep {
 };
 
 // How a batch class (a padded batch size up to 256) divides the pack for
-// k_fwd_s: groups of whole models, widest first.
-struct StepPlan {
-  int slots = 0;                   // workgroups of k_fwd_s the device holds (0: no instance)
+// k_fwd_s: groups of whole models, widest first.  Made by the first forward
+// pass of the class.
+struct FwdPlan {
+  int slots = -1;              // workgroups the device holds (0: no instance, -1: not asked yet)
   int32_t ngroups = 0;
-  const StepGroup* groups = nullptr;  // in the handle's one allocation
+  StepGroup* groups = nullptr;
 };
 constexpr int kStepClasses = 5;
 constexpr int32_t kStepBatch[kStepClasses] = {16, 32, 64, 128, 256};
@@ -125,9 +126,8 @@ struct pmlp {
   int32_t* d_act = nullptr;
   int32_t* d_mid = nullptr;   // [Npad] model of each hidden unit
   int32_t* d_actn = nullptr;  // [Npad] activation id of each hidden unit
-  int32_t* d_uinfo = nullptr; // [Npad] the same, + 256 at the last unit of a model
-  StepPlan plan[kStepClasses];
-  StepGroup* d_groups = nullptr;
+  int32_t* d_uinfo = nullptr; // [Npad] the same, + 256 at the last unit of a model (with a plan)
+  FwdPlan plan[kStepClasses];
   int32_t widest = 0;  // units of the widest model
   Tile3* d_tiles = nullptr;
   int32_t* d_order = nullptr;  // tile indices, widest first
@@ -182,7 +182,10 @@ void release(pmlp* h) {
   dfree(h->d_mid);
   dfree(h->d_actn);
   dfree(h->d_uinfo);
-  dfree(h->d_groups);
+  for (FwdPlan& p : h->plan) {
+    dfree(p.groups);
+    p = FwdPlan{};
+  }
   dfree(h->d_tiles);
   dfree(h->d_order);
   dfree(h->loss);
@@ -566,33 +569,51 @@ std::vector<StepGroup> step_groups(const std::vector<int32_t>& hs, int64_t N, in
   return g;
 }
 
-// The plans of every batch class whose kernels take this pack's shape.
-int build_step_plans(pmlp* h) {
-  h->widest = *std::max_element(h->hs.begin(), h->hs.end());
-  std::vector<StepGroup> all;
-  size_t at[kStepClasses] = {};
-  for (int c = 0; c < kStepClasses; ++c) {
-    if (kStepBatch[c] >= 64 && h->N < kSplitUnits) break;
-    StepPlan& p = h->plan[c];
-    p.slots = fwd_s_slots(c, h->F4, h->O);
-    if (p.slots <= 0) continue;
-    const std::vector<StepGroup> g = step_groups(h->hs, h->N, p.slots);
-    at[c] = all.size();
-    all.insert(all.end(), g.begin(), g.end());
-    p.ngroups = (int32_t)g.size();
+// Whether class c has a plan, which the first call makes (a handle that only
+// trains, or uses the bf16 modes, has none: for 10,000 models the five plans
+// took 0.4 ms of a creation of 1.1).  False where the kernels do not take the
+// pack's shape, or device memory is short; nothing is changed then, and the
+// other kernels need no plan.  While the handle's stream is being captured the
+// plan is made beside it, on a stream of its own, and none of that is recorded.
+bool forward_plan(pmlp* h, int c) {
+  FwdPlan& p = h->plan[c];
+  if (p.slots < 0)
+    p.slots = kStepBatch[c] >= 64 && h->N < kSplitUnits ? 0 : fwd_s_slots(c, h->F4, h->O);
+  if (p.slots == 0 || p.groups) return p.slots > 0;
+  const std::vector<StepGroup> g = step_groups(h->hs, h->N, p.slots);
+  const size_t bytes = g.size() * sizeof(StepGroup);
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  hipStream_t s = h->stream;
+  bool ok = hipStreamIsCapturing(h->stream, &st) == hipSuccess;
+  const bool beside = ok && st != hipStreamCaptureStatusNone;
+  if (beside) {
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    s = nullptr;
+    ok = hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess;
   }
-  if (all.empty()) return PMLP_OK;
-  if (hipMalloc(&h->d_uinfo, (size_t)h->Npad * sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(&h->d_groups, all.size() * sizeof(StepGroup)) != hipSuccess) {
+  StepGroup* groups = nullptr;
+  int32_t* uinfo = nullptr;
+  ok = ok && hipMalloc(&groups, bytes) == hipSuccess &&
+       hipMemcpyAsync(groups, g.data(), bytes, hipMemcpyHostToDevice, s) == hipSuccess;
+  if (!h->d_uinfo)
+    ok = ok && hipMalloc(&uinfo, (size_t)h->Npad * sizeof(int32_t)) == hipSuccess &&
+         launch_unit_info(h->d_mid, h->d_actn, h->N, h->Npad, uinfo, s) == hipSuccess;
+  if (!beside || s) ok = hipStreamSynchronize(s) == hipSuccess && ok;  // (g is read until here)
+  if (beside) {
+    if (s) (void)hipStreamDestroy(s);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  if (!ok) {
     (void)hipGetLastError();
-    return fail(PMLP_ENOMEM, "device allocation failed for the step plans");
+    dfree(groups);
+    dfree(uinfo);
+    return false;
   }
-  PMLP_HIP(hipMemcpy(h->d_groups, all.data(), all.size() * sizeof(StepGroup),
-                     hipMemcpyHostToDevice));
-  PMLP_HIP(launch_unit_info(h->d_mid, h->d_actn, h->N, h->Npad, h->d_uinfo, h->stream));
-  PMLP_HIP(hipStreamSynchronize(h->stream));
-  for (int c = 0; c < kStepClasses; ++c) h->plan[c].groups = h->d_groups + at[c];
-  return PMLP_OK;
+  p.groups = groups;
+  p.ngroups = (int32_t)g.size();
+  if (uinfo) h->d_uinfo = uinfo;
+  return true;
 }
 
 // Whether a forward pass over nchunk batches of class c runs as k_fwd_s.  A
@@ -605,16 +626,16 @@ int build_step_plans(pmlp* h) {
 // (stays) and widths up to 400, 83 / 63; packs of 1,000 to 20,000 units and
 // batches of 16, widths up to 64 and 100, 19 / 11 and 19 / 16; up to 200, 20 /
 // 24 (stays).
-bool fwd_split(const pmlp* h, int c, int64_t nchunk) {
-  if (c < 0 || !h->lds_kernels || bf16_mode(h) || h->deep || h->plan[c].slots <= 0) return false;
+bool fwd_split(pmlp* h, int c, int64_t nchunk) {
+  if (c < 0 || !h->lds_kernels || bf16_mode(h) || h->deep) return false;
   if (h->fused_forward && fwd_m3_supported(kStepBatch[c], h->F4, h->O)) return false;
-  return h->widest <= 128 + h->N * kStepBatch[c] * nchunk / 50000;
+  return h->widest <= 128 + h->N * kStepBatch[c] * nchunk / 50000 && forward_plan(h, c);
 }
 
 // The sample-split forward of B samples in nchunk batches of class c: logits
 // out[b][m][o].
 int forward_split(pmlp* h, int c, const float* X, int32_t B, int32_t nchunk, float* out) {
-  const StepPlan& p = h->plan[c];
+  const FwdPlan& p = h->plan[c];
   FwdSArgs f{};
   f.X = X;
   f.B = B;
@@ -1129,6 +1150,7 @@ int pmlp_create_ex(pmlp_t* out, int32_t F, int32_t O, int32_t M, const int32_t* 
   if (const char* env = getenv("PMLP_GENERIC_KERNELS")) h->lds_kernels = env[0] == '0';
   if (const char* env = getenv("PMLP_FUSED_FORWARD")) h->fused_forward = env[0] == '1';
   h->hs.assign(hidden_sizes, hidden_sizes + M);
+  h->widest = *std::max_element(h->hs.begin(), h->hs.end());
   h->acts.assign(act_ids, act_ids + M);
   h->seg_off.resize((size_t)M + 1);
   h->seg_off[0] = 0;
@@ -1191,7 +1213,6 @@ int pmlp_create_ex(pmlp_t* out, int32_t F, int32_t O, int32_t M, const int32_t* 
                        hipMemcpyHostToDevice));
     PMLP_HIP(hipMemcpy(h->d_actn, actn.data(), (size_t)Npad * sizeof(int32_t),
                        hipMemcpyHostToDevice));
-    if (int rc = build_step_plans(h)) return rc;
     PMLP_HIP(hipMemset(h->W1, 0, w1_bytes));
     PMLP_HIP(hipMemset(h->W2, 0, (size_t)O * Npad * sizeof(float)));
     PMLP_HIP(hipMemcpy(h->d_tiles, tiles.data(), tiles.size() * sizeof(Tile3),

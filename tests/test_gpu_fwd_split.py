@@ -232,3 +232,42 @@ def test_handles_of_one_kernel_and_two_shapes(pm, orc, torch):
             assert err_logits(got, orc.forward(hs, acts, W1, W2, X)).max() <= TOL_STEP
     for net, *_ in nets:
         net.close()
+
+
+def test_a_handle_that_does_not_forward_has_no_plan(pm, torch):
+    """The forward pass's per-unit words (4 bytes a unit) are made by the first
+    forward pass, not with the handle."""
+    hs = np.full(16000, 1000, np.int32)
+    n = int(hs.sum())
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    net = pm.PackedMLP(4, 2, hs, np.zeros(len(hs), np.int32), seed=1)
+    used = before - torch.cuda.mem_get_info()[0]
+    weights, index = 4 * n * (4 + 2), 2 * 4 * n    # W1, W2; model and activation of each unit
+    assert used < weights + index + 4 * n // 2
+    net.close()
+
+
+@pytest.mark.parametrize("mode", ["global", "relaxed"])
+def test_first_forward_may_be_captured(pm, torch, mode):
+    """A first forward pass makes its plan beside the capture it is part of, and
+    replays equal the eager pass."""
+    hs, acts, X, _ = inputs(50, 2, 256, "mixed")
+    e_net = pm.PackedMLP(50, 2, hs, acts, seed=8)
+    g_net = pm.PackedMLP(50, 2, hs, acts, seed=8)
+    xs = [dev(torch, X), dev(torch, X[::-1].copy())]
+    Xd, out = torch.empty_like(xs[0]), torch.empty(256, len(hs), 2, device="cuda")
+    want = [e_net.forward(x) for x in xs]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode=mode):
+        g_net.forward(Xd, out)
+    assert g_net.kernel_variants()["fwd_m3"][0] == "k_fwd_s"
+    for rep in range(4):
+        Xd.copy_(xs[rep % 2])
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[rep % 2]), rep
+        assert torch.equal(e_net.forward(xs[0]), want[0])
+    for net in (g_net, e_net):
+        net.close()
