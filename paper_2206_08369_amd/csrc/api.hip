@@ -1105,6 +1105,27 @@ void build_tiles(const std::vector<int32_t>& hs, int64_t cap, std::vector<Tile3>
   if (cur.len > 0) tiles.push_back(cur);
 }
 
+// Forward pass by the batch copy, the product and the M3 forward (in two
+// kernels or, fused_forward, one): logits out[b][m][o], not over X.
+int forward_logits(pmlp* h, const float* X, int32_t B, int32_t Bp, float* out) {
+  const Work w = handle_work(h);
+  const int64_t sm = h->O, sb = (int64_t)h->M * h->O, nout = (int64_t)B * sb;
+  if (PmlpDeep* d = h->deep) {
+    if (int rc = ensure_deep_workspace(h, Bp)) return rc;
+    if (int rc = forward_deep(h, X, B, Bp, w, out, d->has_split2 ? nout : 0)) return rc;
+    return run(h, KID_M3_FWD, [&] {
+      return launch_m3_fwd(d->Zt2, Bp, B, h->W2, d->N2pad, h->O, d->d_off2, h->d_act, d->d_tiles2,
+                           d->d_order2, d->ntiles2, nullptr, out, sm, sb, h->stream);
+    });
+  }
+  if (forward_fused(h, Bp)) return forward_m3(h, X, B, Bp, w, out, sm, sb, nout);
+  if (int rc = forward_hidden(h, X, B, Bp, w, out, h->has_split ? nout : 0)) return rc;
+  return run(h, KID_M3_FWD, [&] {
+    return launch_m3_fwd(h->Zt, Bp, B, h->W2, h->Npad, h->O, h->d_seg_off, h->d_act, h->d_tiles,
+                         h->d_order, h->ntiles, h->b2, out, sm, sb, h->stream, z_bf16(h));
+  });
+}
+
 }  // namespace
 
 extern "C" {
@@ -1272,7 +1293,19 @@ int pmlp_forward(pmlp_t h, const float* X_dev, int32_t B, float* logits_dev) {
   if (int rc = check_batch(h, X_dev, B)) return rc;
   if (!logits_dev) return fail(PMLP_EINVAL, "null logits");
   const int32_t Bp = pad_batch(B);
+  const int64_t nout = (int64_t)B * h->M * h->O;
   if (int rc = use_device(h)) return rc;
+  // Logits over X itself go through the workspace: k_fwd_s and the batch copy
+  // read X while they write (clear) logits.
+  const uintptr_t x0 = (uintptr_t)X_dev, x1 = x0 + (size_t)B * h->F * sizeof(float);
+  const uintptr_t l0 = (uintptr_t)logits_dev, l1 = l0 + (size_t)nout * sizeof(float);
+  if (x0 < l1 && l0 < x1) {
+    if (int rc = ensure_workspace(h, Bp)) return rc;
+    if (int rc = forward_logits(h, X_dev, B, Bp, h->LG)) return rc;
+    return run(h, KID_AUX, [&] {
+      return launch_copy_rows(logits_dev, 1, h->LG, 1, nout, 1, h->stream);
+    });
+  }
   {
     // one launch, whatever the batch: runs of 256 samples (or of 128 or 64
     // where that pads the batch less)
@@ -1290,28 +1323,7 @@ int pmlp_forward(pmlp_t h, const float* X_dev, int32_t B, float* logits_dev) {
       return forward_split(h, cls, X_dev, B, nchunk, logits_dev);
   }
   if (int rc = ensure_workspace(h, Bp)) return rc;
-  if (PmlpDeep* d = h->deep) {
-    if (int rc = ensure_deep_workspace(h, Bp)) return rc;
-    if (int rc = forward_deep(h, X_dev, B, Bp, handle_work(h), logits_dev,
-                              d->has_split2 ? (int64_t)B * h->M * h->O : 0))
-      return rc;
-    return run(h, KID_M3_FWD, [&] {
-      return launch_m3_fwd(d->Zt2, Bp, B, h->W2, d->N2pad, h->O, d->d_off2, h->d_act, d->d_tiles2,
-                           d->d_order2, d->ntiles2, nullptr, logits_dev, h->O,
-                           (int64_t)h->M * h->O, h->stream);
-    });
-  }
-  if (forward_fused(h, Bp))
-    return forward_m3(h, X_dev, B, Bp, handle_work(h), logits_dev, h->O, (int64_t)h->M * h->O,
-                      (int64_t)B * h->M * h->O);
-  if (int rc = forward_hidden(h, X_dev, B, Bp, handle_work(h), logits_dev,
-                              h->has_split ? (int64_t)B * h->M * h->O : 0))
-    return rc;
-  return run(h, KID_M3_FWD, [&] {
-    return launch_m3_fwd(h->Zt, Bp, B, h->W2, h->Npad, h->O, h->d_seg_off, h->d_act, h->d_tiles,
-                         h->d_order, h->ntiles, h->b2, logits_dev, h->O, (int64_t)h->M * h->O,
-                         h->stream, z_bf16(h));
-  });
+  return forward_logits(h, X_dev, B, Bp, logits_dev);
 }
 
 int pmlp_train_step(pmlp_t h, const float* X_dev, const int32_t* y_dev, int32_t B, float lr) {

@@ -271,3 +271,23 @@ def test_first_forward_may_be_captured(pm, torch, mode):
         assert torch.equal(e_net.forward(xs[0]), want[0])
     for net in (g_net, e_net):
         net.close()
+
+
+@pytest.mark.parametrize("F,O,B,kind", [(50, 2, 200, "mixed"), (104, 4, 16, "few"),
+                                        (150, 2, 300, "wide"), (50, 2, 1000, "mixed")])
+def test_logits_may_lie_over_the_samples(pm, torch, F, O, B, kind):
+    """Logits written over the samples they come from (before, across the end
+    of and exactly on them) equal those written elsewhere to the order of their
+    sums."""
+    hs, acts, X, _ = inputs(F, O, B, kind)
+    net = pm.PackedMLP(F, O, hs, acts, seed=11)
+    M = len(hs)
+    want = net.forward(dev(torch, X)).cpu().numpy()
+    for at in (0, B * F // 2, B * M * O - 1):       # the samples' place in the buffer
+        buf = torch.zeros(max(B * M * O, at + B * F), device="cuda")
+        buf[at:at + B * F] = dev(torch, X).reshape(-1)
+        net._stream()
+        pm.pmlp_forward(net.handle, buf.data_ptr() + 4 * at, B, buf.data_ptr())
+        got = buf[:B * M * O].reshape(B, M, O).cpu().numpy()
+        assert err_logits(got, want).max() <= TOL_STEP
+    net.close()
