@@ -846,7 +846,7 @@ int step(pmlp* h, const float* X, const void* y, int32_t B, float lr, const floa
     return PMLP_OK;
   }
   if (int rc = run(h, KID_M3_BWD, [&] {
-        return launch_m3_bwd(w.Zt, bf16_mode(h) ? h->dZ16 : nullptr, Bp, h->W2, h->N, h->Npad,
+        return launch_m3_bwd(w.Zt, bf16_mode(h) ? h->dZ16 : nullptr, Bp, h->W2, h->N, h->M, h->Npad,
                              h->O, h->d_mid, h->d_seg_off,
                              h->d_act, w.LG, lr, lrm, dW2, h->stream, z_bf16(h));
       }))
@@ -995,7 +995,7 @@ int step_deep(pmlp* h, const float* X, const int32_t* y, int32_t B, float lr, fl
     return rc;
   // dZ2 over Z2 in place; W2 updated (or dW2 stored)
   if (int rc = run(h, KID_M3_BWD, [&] {
-        return launch_m3_bwd(d->Zt2, nullptr, Bp, h->W2, d->N2, d->N2pad, h->O, d->d_mid2,
+        return launch_m3_bwd(d->Zt2, nullptr, Bp, h->W2, d->N2, h->M, d->N2pad, h->O, d->d_mid2,
                              d->d_off2, h->d_act, w.LG, lr, nullptr, dW2, h->stream);
       }))
     return rc;

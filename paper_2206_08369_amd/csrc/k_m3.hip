@@ -342,15 +342,34 @@ hipError_t launch_m3_fwd(const float* Zt, int32_t Bp, int32_t B, const float* W2
 // passes; W2 is updated once at the end.
 // ---------------------------------------------------------------------------
 
-// Units per wave: at most kRunMax (long runs reload G and the segment data
-// least), halved down to kRunMin until the launch has kRunWaves waves.  A wave
-// walks its run one segment and one pass of the batch after the other, so a
-// launch of few waves lasts as long as one of them and leaves the memory
-// idle: with 256 units per wave at 201,000 units and 1,024 samples (785 waves)
-// it took 1096 us for 1.65 GB; with 16, a step there takes 0.79 ms less, and
-// one of 51,000 units and 1,000 samples 0.46 ms instead of 1.23.
-static constexpr int kRunMax = 256, kRunMin = 16;
-static constexpr int64_t kRunWaves = 16384;
+// Units per wave, 16 to 256.  A wave walks its run one segment and one pass of
+// the batch after the other, so a launch of few waves lasts as long as one of
+// them and leaves the memory idle; where a long run is less than a model it
+// reloads G and the segment's data least, and a batch of up to 16 samples takes
+// 64 units in one round of loads.  So the run is as long as leaves kRunWaves
+// waves (seven eighths of the 4,096 the device holds at 4 per SIMD), twice as
+// many for batches above 64 samples, where each lasts longer, and no longer than
+// six models of mean width, each of which is a chain of loads of its own; 256
+// units take 16,384 waves to be better than 128 there.  Measured, us a step in
+// bf16 mode, runs of 16 / 32 / 64 / 128 / 256 (the rule's in brackets):
+//   53,875 units of 1..998, 1,000 samples, 16 outputs  [763] 743 1065 1795 3292
+//   188,544 of 384, 1 sample            141 [121]  120   114   130
+//   201,000 of 1..200, 1,024 samples: 32 take 0.1 of 1.7 ms more than 16
+//   507,885 of 1..100, 1 sample         236  226   219  [216]  223
+//   507,885 of 1..100, 256 samples      667  658  [659]  658   724
+//   1,007,940 of 1..100, 64 samples     622  573   551   537  [526]
+//   1,512,275 of 1..100, 256 samples   1603 1570  1566 [1578] 1650
+//   1,200,000 of 4, 64 samples        [1014] 1019 1030  1102  1216
+//   20,000 of 1, 64 samples            [133]  152  230   396   710
+static constexpr int64_t kRunWaves = 3584;
+
+static int bwd_run(int64_t N, int32_t M, int32_t Bp) {
+  const int64_t waves = Bp <= 64 ? kRunWaves : 2 * kRunWaves;
+  const int most = Bp <= 64 || N >= (int64_t)16384 * 256 ? 256 : 128;
+  int run = 16;
+  while (run < most && 2 * run * waves <= N && 2 * run * (int64_t)M <= 6 * N) run <<= 1;
+  return run;
+}
 
 template <int OM, int A, bool ZB>
 __device__ __forceinline__ void bwd_segment(float* __restrict__ Zt,
@@ -486,7 +505,7 @@ __global__ __launch_bounds__(kBlock) void k_m3_bwd(
 
 template <int OM>
 static void m3_bwd_dispatch(float* Zt, bool zb, unsigned short* dZ16, int32_t Bp, float* W2, int64_t N,
-                            int64_t ldw, int32_t O, const int32_t* mid, const int64_t* seg_off,
+                            int32_t M, int64_t ldw, int32_t O, const int32_t* mid, const int64_t* seg_off,
                             const int32_t* act, const float* G, float lr, const float* lrm,
                             float* dW2, hipStream_t s) {
   int LG = 64;
@@ -496,8 +515,7 @@ static void m3_bwd_dispatch(float* Zt, bool zb, unsigned short* dZ16, int32_t Bp
     while (LG < q) LG <<= 1;
   }
   const int slots = ceil_div_i(Bp, 4 * LG);
-  int run = kRunMax;
-  while (run > kRunMin && N < kRunWaves * run) run >>= 1;
+  const int run = bwd_run(N, M, Bp);
   const size_t lds = (size_t)4 * run * OM * sizeof(float);
   const int64_t waves = (N + run - 1) / run;
   const unsigned blocks = (unsigned)((waves + 3) / 4);
@@ -516,15 +534,15 @@ static void m3_bwd_dispatch(float* Zt, bool zb, unsigned short* dZ16, int32_t Bp
 }
 
 hipError_t launch_m3_bwd(float* Zt, unsigned short* dZ16, int32_t Bp, float* W2, int64_t N,
-                         int64_t ldw, int32_t O, const int32_t* mid, const int64_t* seg_off,
+                         int32_t M, int64_t ldw, int32_t O, const int32_t* mid, const int64_t* seg_off,
                          const int32_t* act, const float* G, float lr, const float* lrm,
                          float* dW2, hipStream_t s, bool zb) {
   note_variant("k_m3_bwd", kArithNone);
-  if (O <= 2) m3_bwd_dispatch<2>(Zt, zb, dZ16, Bp, W2, N, ldw, O, mid, seg_off, act, G, lr, lrm, dW2, s);
-  else if (O <= 4) m3_bwd_dispatch<4>(Zt, zb, dZ16, Bp, W2, N, ldw, O, mid, seg_off, act, G, lr, lrm, dW2, s);
-  else if (O <= 8) m3_bwd_dispatch<8>(Zt, zb, dZ16, Bp, W2, N, ldw, O, mid, seg_off, act, G, lr, lrm, dW2, s);
-  else if (O <= 10) m3_bwd_dispatch<10>(Zt, zb, dZ16, Bp, W2, N, ldw, O, mid, seg_off, act, G, lr, lrm, dW2, s);
-  else m3_bwd_dispatch<16>(Zt, zb, dZ16, Bp, W2, N, ldw, O, mid, seg_off, act, G, lr, lrm, dW2, s);
+  if (O <= 2) m3_bwd_dispatch<2>(Zt, zb, dZ16, Bp, W2, N, M, ldw, O, mid, seg_off, act, G, lr, lrm, dW2, s);
+  else if (O <= 4) m3_bwd_dispatch<4>(Zt, zb, dZ16, Bp, W2, N, M, ldw, O, mid, seg_off, act, G, lr, lrm, dW2, s);
+  else if (O <= 8) m3_bwd_dispatch<8>(Zt, zb, dZ16, Bp, W2, N, M, ldw, O, mid, seg_off, act, G, lr, lrm, dW2, s);
+  else if (O <= 10) m3_bwd_dispatch<10>(Zt, zb, dZ16, Bp, W2, N, M, ldw, O, mid, seg_off, act, G, lr, lrm, dW2, s);
+  else m3_bwd_dispatch<16>(Zt, zb, dZ16, Bp, W2, N, M, ldw, O, mid, seg_off, act, G, lr, lrm, dW2, s);
   return hipGetLastError();
 }
 

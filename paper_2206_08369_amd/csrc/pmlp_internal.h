@@ -288,7 +288,7 @@ hipError_t launch_mse(float* LG, const float* Y, int32_t M, int32_t Bp, int32_t 
 // dZ16 set, as bf16 into dZ16 [Npad][Bp] leaving Zt unchanged; then the W2
 // update (dW2 null) or the dW2 store.
 hipError_t launch_m3_bwd(float* Zt, unsigned short* dZ16, int32_t Bp, float* W2, int64_t N,
-                         int64_t ldw, int32_t O, const int32_t* mid, const int64_t* seg_off,
+                         int32_t M, int64_t ldw, int32_t O, const int32_t* mid, const int64_t* seg_off,
                          const int32_t* act, const float* G, float lr, const float* lrm,
                          float* dW2, hipStream_t s, bool zb = false);
 

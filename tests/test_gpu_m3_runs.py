@@ -1,7 +1,8 @@
 """The M3 backward's units per wave (k_m3_bwd) follow the pack's size: 16 for
-small packs, then 32, 64, ... up to 256.  One gradient step at a size of each
-of the first three, with runs that split models and models inside one run,
-against the fp64 oracle on a sample of the models (they are independent)."""
+small packs, then 32, 64, 128 and, for batches of up to 64 samples, 256.  One
+gradient step at a size of each, with runs that split models and models inside
+one run, against the fp64 oracle on a sample of the models (they are
+independent)."""
 import numpy as np
 import pytest
 
@@ -28,11 +29,14 @@ def pm(torch):
     return pm
 
 
-# (units wanted, O, B): 16, 32 and 64 units per wave; one and two passes over
-# the batch, three and four outputs
-@pytest.mark.parametrize("units,O,B", [(3000, 3, 260), (550000, 3, 270), (1100000, 4, 290)])
+# (units wanted, O, B): 16, 64, 128, 32, 64, 128, 256 and 256 units per wave; one
+# and two passes over the batch, three to sixteen outputs (at sixteen, 256 units
+# take all of the 64 KB of LDS that a launch has without asking)
+@pytest.mark.parametrize("units,O,B", [(3000, 3, 260), (550000, 3, 270), (1100000, 4, 290),
+                                       (130000, 3, 33), (250000, 10, 20), (500000, 16, 40),
+                                       (1000000, 16, 9), (1000000, 3, 64)])
 def test_units_per_wave(pm, orc, torch, units, O, B):
-    F = 6 if O == 3 else 200   # (four outputs: past the fused backward's columns)
+    F = 6 if O == 3 else 200   # (other outputs: past the fused backward's columns)
     rng = np.random.default_rng(units)
     hs = rng.integers(1, 300, units // 150).astype(np.int32)
     acts = rng.integers(0, 10, len(hs)).astype(np.int32)
