@@ -86,6 +86,7 @@ struct PmlpDeep {
   Tile3* d_tiles2 = nullptr;  // M3 forward tiles of the second layer
   int32_t* d_order2 = nullptr;
   int32_t ntiles2 = 0;
+  int32_t npacked2 = 0;
   bool has_split2 = false;
   SegUnit* d_ufwd = nullptr;  // row blocks of the second layer
   int32_t nufwd = 0;
@@ -132,6 +133,7 @@ struct pmlp {
   Tile3* d_tiles = nullptr;
   int32_t* d_order = nullptr;  // tile indices, widest first
   int32_t ntiles = 0;
+  int32_t npacked = 0;  // tiles of another list behind those (m3_plan), or 0
   bool has_split = false;
   float* loss = nullptr;   // [M]
   int32_t* flag = nullptr; // [4]: bad label, bad rate, count of non-finite losses, spare
@@ -1071,16 +1073,9 @@ int64_t tile_cap(int64_t N) {
   return cap;
 }
 
-void build_tiles(const std::vector<int32_t>& hs, int64_t cap, std::vector<Tile3>& tiles,
-                 bool& has_split) {
-  tiles.clear();
+void build_tiles(const std::vector<int32_t>& hs, int64_t cap, bool alone,
+                 std::vector<Tile3>& tiles, bool& has_split) {
   has_split = false;
-  // A pack of few models at the smallest cap has waves to spare and its launch
-  // lasts as long as its longest tile, a chain of a few trips to memory per
-  // model: one model a tile, with the same sums (60 models of 1..10 units, an
-  // epoch of 32 steps: 986 -> 757 us).  (At most kTile3Count tiles:
-  // 2^20 samples of them are 2^31 threads, a grid's limit is 2^32.)
-  const bool alone = cap == kTile3Min && 2 * (int64_t)hs.size() <= kTile3Count;
   Tile3 cur{0, 0, 0, 0, 0};
   int64_t n = 0;
   for (size_t m = 0; m < hs.size(); ++m) {
@@ -1105,6 +1100,48 @@ void build_tiles(const std::vector<int32_t>& hs, int64_t cap, std::vector<Tile3>
   if (cur.len > 0) tiles.push_back(cur);
 }
 
+// A pack's tiles and the order its launches take them in (widest first, ties in
+// plan order, so that the dispatcher schedules the longest work first).
+struct M3Plan {
+  std::vector<Tile3> tiles;    // n of them, then npacked of a second list
+  std::vector<int32_t> order;  // places within each list
+  int32_t n = 0, npacked = 0;
+  bool has_split = false;
+};
+
+// A pack of few models at the smallest cap has waves to spare and its launch
+// lasts as long as its longest tile, a chain of a few trips to memory per
+// model: one model a tile, with the same sums (60 models of 1..10 units, an
+// epoch of 32 steps: 986 -> 757 us; 1,024 models of one unit, ten outputs, a
+// forward pass of 1,000 samples: 117 -> 42 us).  (At most kTile3Count tiles:
+// 2^20 samples of them are 2^31 threads, a grid's limit is 2^32.)
+// One case prefers tiles of several models whose logits lie side by side:
+// forward passes (logits [b][m][o]) of 8 to 15 outputs, whose 32 to 60 bytes a
+// store are parts of lines, once the logits exceed what the caches merge them
+// in.  1,024 models of one unit, us, one model a tile / several: 10 outputs,
+// 10,000 samples (0.4 GB) 363 / 458; 20,000 (0.8 GB) 761 / 782, of six units
+// 905 / 861; 50,000 (2 GB) 2748 / 1819; 7 outputs, 50,000, 1417 / 1626; 16
+// outputs 1800 / 1987.  Such packs have both lists.
+constexpr int64_t kPackedLogits = (int64_t)128 << 20;  // floats
+
+M3Plan m3_plan(const std::vector<int32_t>& hs, int64_t N, int32_t O) {
+  M3Plan p;
+  const int64_t cap = tile_cap(N);
+  const bool alone = cap == kTile3Min && 2 * (int64_t)hs.size() <= kTile3Count;
+  build_tiles(hs, cap, alone, p.tiles, p.has_split);
+  p.n = (int32_t)p.tiles.size();
+  if (alone && O >= 8 && O <= 15) build_tiles(hs, cap, false, p.tiles, p.has_split);
+  p.npacked = (int32_t)p.tiles.size() - p.n;
+  p.order.resize(p.tiles.size());
+  for (int32_t l = 0; l < 2; ++l) {
+    const Tile3* t = p.tiles.data() + (l ? p.n : 0);
+    auto o = p.order.begin() + (l ? p.n : 0), e = l ? p.order.end() : o + p.n;
+    for (auto it = o; it != e; ++it) *it = (int32_t)(it - o);
+    std::stable_sort(o, e, [&](int32_t x, int32_t y) { return t[x].len > t[y].len; });
+  }
+  return p;
+}
+
 // Forward pass by the batch copy, the product and the M3 forward (in two
 // kernels or, fused_forward, one): logits out[b][m][o], not over X.
 int forward_logits(pmlp* h, const float* X, int32_t B, int32_t Bp, float* out) {
@@ -1113,16 +1150,20 @@ int forward_logits(pmlp* h, const float* X, int32_t B, int32_t Bp, float* out) {
   if (PmlpDeep* d = h->deep) {
     if (int rc = ensure_deep_workspace(h, Bp)) return rc;
     if (int rc = forward_deep(h, X, B, Bp, w, out, d->has_split2 ? nout : 0)) return rc;
+    const int32_t at = d->npacked2 && nout > kPackedLogits ? d->ntiles2 : 0;
     return run(h, KID_M3_FWD, [&] {
-      return launch_m3_fwd(d->Zt2, Bp, B, h->W2, d->N2pad, h->O, d->d_off2, h->d_act, d->d_tiles2,
-                           d->d_order2, d->ntiles2, nullptr, out, sm, sb, h->stream);
+      return launch_m3_fwd(d->Zt2, Bp, B, h->W2, d->N2pad, h->O, d->d_off2, h->d_act,
+                           d->d_tiles2 + at, d->d_order2 + at, at ? d->npacked2 : d->ntiles2,
+                           nullptr, out, sm, sb, h->stream);
     });
   }
   if (forward_fused(h, Bp)) return forward_m3(h, X, B, Bp, w, out, sm, sb, nout);
   if (int rc = forward_hidden(h, X, B, Bp, w, out, h->has_split ? nout : 0)) return rc;
+  const int32_t at = h->npacked && nout > kPackedLogits ? h->ntiles : 0;
   return run(h, KID_M3_FWD, [&] {
-    return launch_m3_fwd(h->Zt, Bp, B, h->W2, h->Npad, h->O, h->d_seg_off, h->d_act, h->d_tiles,
-                         h->d_order, h->ntiles, h->b2, out, sm, sb, h->stream, z_bf16(h));
+    return launch_m3_fwd(h->Zt, Bp, B, h->W2, h->Npad, h->O, h->d_seg_off, h->d_act,
+                         h->d_tiles + at, h->d_order + at, at ? h->npacked : h->ntiles, h->b2, out,
+                         sm, sb, h->stream, z_bf16(h));
   });
 }
 
@@ -1183,15 +1224,10 @@ int pmlp_create_ex(pmlp_t* out, int32_t F, int32_t O, int32_t M, const int32_t* 
       mid[n] = m;
       actn[n] = act_ids[m];
     }
-  std::vector<Tile3> tiles;
-  build_tiles(h->hs, tile_cap(N), tiles, h->has_split);
-  h->ntiles = (int32_t)tiles.size();
-  // the M3 forward launches its waves widest tile first (ties in plan order),
-  // so the dispatcher schedules the longest work first
-  std::vector<int32_t> order(tiles.size());
-  for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)i;
-  std::stable_sort(order.begin(), order.end(),
-                   [&](int32_t x, int32_t y) { return tiles[x].len > tiles[y].len; });
+  const M3Plan m3 = m3_plan(h->hs, N, O);
+  h->ntiles = m3.n;
+  h->npacked = m3.npacked;
+  h->has_split = m3.has_split;
   std::vector<float> bound2((size_t)M);
   for (int32_t m = 0; m < M; ++m) bound2[m] = (float)(1.0 / std::sqrt((double)hidden_sizes[m]));
   const float bound1 = (float)(1.0 / std::sqrt((double)F));
@@ -1216,8 +1252,8 @@ int pmlp_create_ex(pmlp_t* out, int32_t F, int32_t O, int32_t M, const int32_t* 
       hipMalloc(&h->d_act, (size_t)M * sizeof(int32_t)) != hipSuccess ||
       hipMalloc(&h->d_mid, (size_t)Npad * sizeof(int32_t)) != hipSuccess ||
       hipMalloc(&h->d_actn, (size_t)Npad * sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(&h->d_tiles, tiles.size() * sizeof(Tile3)) != hipSuccess ||
-      hipMalloc(&h->d_order, order.size() * sizeof(int32_t)) != hipSuccess ||
+      hipMalloc(&h->d_tiles, m3.tiles.size() * sizeof(Tile3)) != hipSuccess ||
+      hipMalloc(&h->d_order, m3.order.size() * sizeof(int32_t)) != hipSuccess ||
       hipMalloc(&h->loss, (size_t)M * sizeof(float)) != hipSuccess ||
       hipMalloc(&h->flag, 4 * sizeof(int32_t)) != hipSuccess ||
       hipMalloc(&d_bound2, (size_t)M * sizeof(float)) != hipSuccess ||
@@ -1236,9 +1272,9 @@ int pmlp_create_ex(pmlp_t* out, int32_t F, int32_t O, int32_t M, const int32_t* 
                        hipMemcpyHostToDevice));
     PMLP_HIP(hipMemset(h->W1, 0, w1_bytes));
     PMLP_HIP(hipMemset(h->W2, 0, (size_t)O * Npad * sizeof(float)));
-    PMLP_HIP(hipMemcpy(h->d_tiles, tiles.data(), tiles.size() * sizeof(Tile3),
+    PMLP_HIP(hipMemcpy(h->d_tiles, m3.tiles.data(), m3.tiles.size() * sizeof(Tile3),
                        hipMemcpyHostToDevice));
-    PMLP_HIP(hipMemcpy(h->d_order, order.data(), order.size() * sizeof(int32_t),
+    PMLP_HIP(hipMemcpy(h->d_order, m3.order.data(), m3.order.size() * sizeof(int32_t),
                        hipMemcpyHostToDevice));
     PMLP_HIP(hipMemcpy(d_bound2, bound2.data(), (size_t)M * sizeof(float), hipMemcpyHostToDevice));
     PMLP_HIP(hipMemset(h->flag, 0, 4 * sizeof(int32_t)));
@@ -1657,13 +1693,10 @@ int pmlp_create_deep(pmlp_t* out, int32_t F, int32_t O, int32_t M, const int32_t
   std::vector<int32_t> mid2((size_t)d->N2pad, M - 1);  // padding rows map to the last model
   for (int32_t m = 0; m < M; ++m)
     for (int64_t n = d->off2[m]; n < d->off2[m + 1]; ++n) mid2[n] = m;
-  std::vector<Tile3> tiles;
-  build_tiles(d->h2, tile_cap(N2), tiles, d->has_split2);
-  d->ntiles2 = (int32_t)tiles.size();
-  std::vector<int32_t> order(tiles.size());
-  for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)i;
-  std::stable_sort(order.begin(), order.end(),
-                   [&](int32_t x, int32_t y) { return tiles[x].len > tiles[y].len; });
+  const M3Plan m3 = m3_plan(d->h2, N2, O);
+  d->ntiles2 = m3.n;
+  d->npacked2 = m3.npacked;
+  d->has_split2 = m3.has_split;
   std::vector<SegUnit> ufwd, uback;
   std::vector<SegTile> tgrad;
   for (int32_t m = 0; m < M; ++m) {
@@ -1698,8 +1731,8 @@ int pmlp_create_deep(pmlp_t* out, int32_t F, int32_t O, int32_t M, const int32_t
       hipMalloc(&d->d_mid2, (size_t)d->N2pad * sizeof(int32_t)) != hipSuccess ||
       hipMalloc(&d->W12, nk * sizeof(float)) != hipSuccess ||
       hipMalloc(&d->G12, nk * sizeof(float)) != hipSuccess ||
-      hipMalloc(&d->d_tiles2, tiles.size() * sizeof(Tile3)) != hipSuccess ||
-      hipMalloc(&d->d_order2, order.size() * sizeof(int32_t)) != hipSuccess ||
+      hipMalloc(&d->d_tiles2, m3.tiles.size() * sizeof(Tile3)) != hipSuccess ||
+      hipMalloc(&d->d_order2, m3.order.size() * sizeof(int32_t)) != hipSuccess ||
       hipMalloc(&d->d_ufwd, ufwd.size() * sizeof(SegUnit)) != hipSuccess ||
       hipMalloc(&d->d_uback, uback.size() * sizeof(SegUnit)) != hipSuccess ||
       hipMalloc(&d->d_tgrad, tgrad.size() * sizeof(SegTile)) != hipSuccess ||
@@ -1722,9 +1755,9 @@ int pmlp_create_deep(pmlp_t* out, int32_t F, int32_t O, int32_t M, const int32_t
     PMLP_HIP(hipMemcpy(d->d_h2, h2, (size_t)M * sizeof(int32_t), hipMemcpyHostToDevice));
     PMLP_HIP(hipMemcpy(d->d_mid2, mid2.data(), (size_t)d->N2pad * sizeof(int32_t),
                        hipMemcpyHostToDevice));
-    PMLP_HIP(hipMemcpy(d->d_tiles2, tiles.data(), tiles.size() * sizeof(Tile3),
+    PMLP_HIP(hipMemcpy(d->d_tiles2, m3.tiles.data(), m3.tiles.size() * sizeof(Tile3),
                        hipMemcpyHostToDevice));
-    PMLP_HIP(hipMemcpy(d->d_order2, order.data(), order.size() * sizeof(int32_t),
+    PMLP_HIP(hipMemcpy(d->d_order2, m3.order.data(), m3.order.size() * sizeof(int32_t),
                        hipMemcpyHostToDevice));
     PMLP_HIP(hipMemcpy(d->d_ufwd, ufwd.data(), ufwd.size() * sizeof(SegUnit),
                        hipMemcpyHostToDevice));

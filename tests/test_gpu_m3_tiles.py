@@ -34,3 +34,20 @@ def test_sums_do_not_depend_on_the_tiles(pm, torch, O, B):  # noqa: F811
     assert np.array_equal(got[0][0], got[1][0])
     assert np.array_equal(got[0][1], got[1][1][:k])
     assert np.array_equal(got[0][2], got[1][2][:, :k])
+
+
+@pytest.mark.parametrize("deep", [False, True])
+def test_tiles_of_large_forward_passes(pm, torch, deep):  # noqa: F811
+    """Logits above 512 MiB of 8 to 15 outputs are stored by tiles of several
+    models; the same samples in two halves, below, by tiles of one."""
+    rng = np.random.default_rng(3)
+    M, F, O, B = 1000, 9, 10, 14000
+    hs = rng.integers(1, 5, M).astype(np.int32)
+    acts = rng.integers(0, 10, M).astype(np.int32)
+    X = torch.from_numpy(rng.standard_normal((B, F)).astype(np.float32)).cuda()
+    net = (pm.DeepPackedMLP(F, O, hs, hs[::-1].copy(), acts, seed=4) if deep
+           else pm.PackedMLP(F, O, hs, acts, seed=4))
+    whole = net.forward(X)
+    parts = torch.cat([net.forward(X[:B // 2]), net.forward(X[B // 2:])])
+    assert torch.equal(whole, parts)
+    net.close()
