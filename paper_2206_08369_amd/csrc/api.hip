@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -99,12 +100,16 @@ struct PmlpDeep {
 };
 
 // How a batch class (a padded batch size up to 256) divides the pack for
-// k_fwd_s: groups of whole models, widest first.  Made by the first forward
-// pass of the class.
+// k_fwd_s: groups of whole models, widest first, for passes of one batch and
+// of many.  Made by the first forward pass that needs it.
+struct FwdGroups {
+  int32_t n = 0;
+  int64_t cost = 0, most = 0;  // of a batch (see forward_run): all groups, the dearest
+  StepGroup* g = nullptr;
+};
 struct FwdPlan {
-  int slots = -1;              // workgroups the device holds (0: no instance, -1: not asked yet)
-  int32_t ngroups = 0;
-  StepGroup* groups = nullptr;
+  int slots = -1;  // workgroups the device holds (0: no instance, -1: not asked yet)
+  FwdGroups one, many;
 };
 constexpr int kStepClasses = 5;
 constexpr int32_t kStepBatch[kStepClasses] = {16, 32, 64, 128, 256};
@@ -185,7 +190,8 @@ void release(pmlp* h) {
   dfree(h->d_actn);
   dfree(h->d_uinfo);
   for (FwdPlan& p : h->plan) {
-    dfree(p.groups);
+    dfree(p.one.g);
+    dfree(p.many.g);
     p = FwdPlan{};
   }
   dfree(h->d_tiles);
@@ -528,7 +534,16 @@ hipError_t launch_fwd_s(int c, const FwdSArgs& a, hipStream_t s) {
 constexpr int64_t kStepGroup = 1024;
 constexpr int64_t kSplitUnits = 1024;
 
-std::vector<StepGroup> step_groups(const std::vector<int32_t>& hs, int64_t N, int slots) {
+//
+// A pass of many batches has workgroups enough without narrow runs, and theirs
+// have at least `least` models, so that the logits a workgroup stores for one
+// sample fill lines (kRunLogits): with runs of one narrow model each, 900 models
+// of two units, 100 features, four outputs and 10,000 samples took 494 us
+// against 229 through the other kernels.
+constexpr int32_t kRunLogits = 32;
+
+std::vector<StepGroup> step_groups(const std::vector<int32_t>& hs, int64_t N, int slots,
+                                   int32_t least) {
   constexpr int64_t kModel = 3;
   const int64_t total = N + kModel * (int64_t)hs.size();
   const int64_t k = ((total + slots - 1) / slots + kStepGroup - 1) / kStepGroup;
@@ -556,7 +571,7 @@ std::vector<StepGroup> step_groups(const std::vector<int32_t>& hs, int64_t N, in
   StepGroup cur{0, 0, 0, 0};
   int64_t n = 0;
   for (size_t m = 0; m < hs.size(); ++m) {
-    if (cur.nm > 0 && cur.len + hs[m] + kModel * (cur.nm + 1) > hi) {
+    if (cur.nm >= least && cur.len + hs[m] + kModel * (cur.nm + 1) > hi) {
       g.push_back(cur);
       cur.nm = 0;
     }
@@ -571,18 +586,25 @@ std::vector<StepGroup> step_groups(const std::vector<int32_t>& hs, int64_t N, in
   return g;
 }
 
-// Whether class c has a plan, which the first call makes (a handle that only
-// trains, or uses the bf16 modes, has none: for 10,000 models the five plans
-// took 0.4 ms of a creation of 1.1).  False where the kernels do not take the
-// pack's shape, or device memory is short; nothing is changed then, and the
-// other kernels need no plan.  While the handle's stream is being captured the
-// plan is made beside it, on a stream of its own, and none of that is recorded.
-bool forward_plan(pmlp* h, int c) {
+// Workgroups of class c that the device holds, or 0.
+int forward_slots(pmlp* h, int c) {
   FwdPlan& p = h->plan[c];
   if (p.slots < 0)
     p.slots = kStepBatch[c] >= 64 && h->N < kSplitUnits ? 0 : fwd_s_slots(c, h->F4, h->O);
-  if (p.slots == 0 || p.groups) return p.slots > 0;
-  const std::vector<StepGroup> g = step_groups(h->hs, h->N, p.slots);
+  return p.slots;
+}
+
+// Makes the groups of class c for passes of one batch or of many, which the
+// first such pass does (a handle that only trains, or uses the bf16 modes, has
+// none: for 10,000 models the plans of five classes took 0.4 ms of a creation of
+// 1.1).  False where device memory is short; nothing is changed then, and the
+// other kernels need no plan.  While the handle's stream is being captured the
+// plan is made beside it, on a stream of its own, and none of that is recorded.
+bool make_groups(pmlp* h, int c, bool many) {
+  FwdGroups& q = many ? h->plan[c].many : h->plan[c].one;
+  if (q.g) return true;
+  const std::vector<StepGroup> g =
+      step_groups(h->hs, h->N, h->plan[c].slots, many ? div_up(kRunLogits, h->O) : 1);
   const size_t bytes = g.size() * sizeof(StepGroup);
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -612,10 +634,95 @@ bool forward_plan(pmlp* h, int c) {
     dfree(uinfo);
     return false;
   }
-  p.groups = groups;
-  p.ngroups = (int32_t)g.size();
+  q.g = groups;
+  q.n = (int32_t)g.size();
+  q.cost = q.most = 0;
+  for (const StepGroup& x : g) {
+    const int64_t tiles = div_up(x.len, 16), stages = div_up(tiles, std::max(1, kStepBatch[c] / 32));
+    const int64_t v = 16 * (tiles + stages) + 3 * x.nm;
+    q.cost += v;
+    q.most = std::max(q.most, v);
+  }
   if (uinfo) h->d_uinfo = uinfo;
   return true;
+}
+
+// How a pass over nchunk batches of class c runs: its groups and the workgroups
+// for each batch.  Null groups where it has none (see make_groups).
+//
+// The cost of a group is its tiles, a tile's time for each stage of one tile a
+// wave (a barrier) and three units for each model (its reduction and logits); of
+// a pass, the rounds of the device times a workgroup's share of the groups and
+// 80 units for its start (8 us at 0.1 us a unit).  Passes of many batches take
+// the runs of at least kRunLogits unless they cost as much (us, one model a run
+// / these: 221 models of 26 units, 75 features, four outputs, 5,152 samples 103 /
+// 86; 1,437 of 21, 52 features, 2,633 samples 160 / 178).  Where slots / nchunk is
+// small, its remainder leaves the device idle (slots = 256, 129 batches: half of
+// it), so that more workgroups in several rounds are better: 1,000 models of
+// 1..100 units, 50 features, 33,000 samples 3724 -> 2077 us.
+struct FwdRun {
+  const FwdGroups* q = nullptr;
+  int32_t wpc = 0;
+};
+
+FwdRun forward_run(pmlp* h, int c, int64_t nchunk) {
+  const FwdPlan& p = h->plan[c];
+  FwdRun best;
+  try {
+    if (!make_groups(h, c, false) || (nchunk > 1 && !make_groups(h, c, true))) return best;
+  } catch (const std::bad_alloc&) {  // host memory for the plan
+    return best;
+  }
+  const int64_t fit = std::max<int64_t>(1, p.slots / nchunk);
+  int64_t least = 0;
+  auto consider = [&](const FwdGroups& q, int64_t percent) {
+    const int64_t last = fit < 8 ? 32 : fit;
+    for (int64_t w = fit < 8 ? 1 : fit; w <= last; ++w) {
+      const int64_t wpc = std::min<int64_t>(w, q.n);
+      const int64_t rounds = (nchunk * wpc + p.slots - 1) / p.slots;
+      const int64_t share = std::max(q.cost * div_up(q.n, wpc) / q.n, q.most);
+      const int64_t cost = rounds * (share + 80) * percent;
+      if (!best.q || cost < least) {
+        least = cost;
+        best = FwdRun{&q, (int32_t)wpc};
+      }
+    }
+  };
+  consider(p.one, 100);
+  if (nchunk > 1) consider(p.many, 115);
+  return best;
+}
+
+// The batch class of a pass over B samples and the batches that is, or -1.  Up
+// to 256 samples are one batch.  More are batches of 64, 128 or 256, whichever
+// pads least; in passes that fill the device (from 2^26 units times samples),
+// whichever costs least: the padded samples, times the tile of W1 that one of a
+// batch's NW waves of 32 samples splits for all (as long as one wave multiplies
+// it), over 1.2 where the device holds three or more waves per SIMD.  Measured,
+// us, batches of 64 / 128 / 256 of 1,000 models of 1..100 units, two outputs: 100
+// features, 10,000 samples 1110 / 928 / 808; 50 features, 10,000 708 / 625 / 659,
+// 300 (of 320 / 384 / 512) 36 / 38 / 46; 334 models of 21 units, one feature, 392
+// samples (of 448 / 512 / 512) 10 / 14 / 14.
+int forward_class(pmlp* h, int32_t B, int32_t Bp, int32_t* nchunk) {
+  const int one = step_class(Bp);
+  *nchunk = 1;
+  if (one >= 0) return forward_slots(h, one) > 0 ? one : -1;
+  const bool full = h->N * B >= (int64_t)1 << 26;
+  int best = -1;
+  double least = 0;
+  for (int c = 2; c < kStepClasses; ++c) {
+    const int nw = kStepBatch[c] / 32, slots = forward_slots(h, c);
+    if (slots <= 0) continue;
+    const int32_t n = div_up(B, kStepBatch[c]);
+    const bool three = slots * nw >= 3 * 1024;  // (of 1,024 SIMDs)
+    double cost = (double)n * kStepBatch[c];
+    if (full) cost *= (1 + 1.0 / nw) / (three ? 1.2 : 1.0);
+    if (best >= 0 && cost > least) continue;
+    least = cost;
+    best = c;
+    *nchunk = n;
+  }
+  return best;
 }
 
 // Whether a forward pass over nchunk batches of class c runs as k_fwd_s.  A
@@ -628,16 +735,15 @@ bool forward_plan(pmlp* h, int c) {
 // (stays) and widths up to 400, 83 / 63; packs of 1,000 to 20,000 units and
 // batches of 16, widths up to 64 and 100, 19 / 11 and 19 / 16; up to 200, 20 /
 // 24 (stays).
-bool fwd_split(pmlp* h, int c, int64_t nchunk) {
-  if (c < 0 || !h->lds_kernels || bf16_mode(h) || h->deep) return false;
+bool fwd_split_pays(const pmlp* h, int c, int64_t nchunk) {
   if (h->fused_forward && fwd_m3_supported(kStepBatch[c], h->F4, h->O)) return false;
-  return h->widest <= 128 + h->N * kStepBatch[c] * nchunk / 50000 && forward_plan(h, c);
+  return h->widest <= 128 + h->N * kStepBatch[c] * nchunk / 50000;
 }
 
 // The sample-split forward of B samples in nchunk batches of class c: logits
 // out[b][m][o].
-int forward_split(pmlp* h, int c, const float* X, int32_t B, int32_t nchunk, float* out) {
-  const FwdPlan& p = h->plan[c];
+int forward_split(pmlp* h, int c, const float* X, int32_t B, int32_t nchunk, const FwdRun& r,
+                  float* out) {
   FwdSArgs f{};
   f.X = X;
   f.B = B;
@@ -646,7 +752,7 @@ int forward_split(pmlp* h, int c, const float* X, int32_t B, int32_t nchunk, flo
   f.O = h->O;
   f.bcol = h->bcol;
   f.nchunk = nchunk;
-  f.wpc = std::max(1, std::min(p.slots / nchunk, p.ngroups));
+  f.wpc = r.wpc;
   f.W1 = h->W1;
   f.W2 = h->W2;
   f.ldw = h->Npad;
@@ -654,8 +760,8 @@ int forward_split(pmlp* h, int c, const float* X, int32_t B, int32_t nchunk, flo
   f.mid = h->d_mid;
   f.uinfo = h->d_uinfo;
   f.seg_off = h->d_seg_off;
-  f.groups = p.groups;
-  f.ngroups = p.ngroups;
+  f.groups = r.q->g;
+  f.ngroups = r.q->n;
   f.out = out;
   f.sm = h->O;
   f.sb = (int64_t)h->M * h->O;
@@ -1342,21 +1448,13 @@ int pmlp_forward(pmlp_t h, const float* X_dev, int32_t B, float* logits_dev) {
       return launch_copy_rows(logits_dev, 1, h->LG, 1, nout, 1, h->stream);
     });
   }
-  {
-    // one launch, whatever the batch: runs of 256 samples (or of 128 or 64
-    // where that pads the batch less)
-    int cls = step_class(Bp);
-    int32_t nchunk = 1;
-    if (cls < 0) {
-      cls = kStepClasses - 1;
-      for (int c = kStepClasses - 2; c >= 2; --c)
-        if ((int64_t)div_up(B, kStepBatch[c]) * kStepBatch[c] <
-            (int64_t)div_up(B, kStepBatch[cls]) * kStepBatch[cls])
-          cls = c;
-      nchunk = div_up(B, kStepBatch[cls]);
+  if (h->lds_kernels && !bf16_mode(h) && !h->deep) {  // one launch, whatever the batch
+    int32_t nchunk = 0;
+    const int c = forward_class(h, B, Bp, &nchunk);
+    if (c >= 0 && fwd_split_pays(h, c, nchunk)) {
+      const FwdRun r = forward_run(h, c, nchunk);
+      if (r.q) return forward_split(h, c, X_dev, B, nchunk, r, logits_dev);
     }
-    if (fwd_split(h, cls, nchunk))
-      return forward_split(h, cls, X_dev, B, nchunk, logits_dev);
   }
   if (int rc = ensure_workspace(h, Bp)) return rc;
   return forward_logits(h, X_dev, B, Bp, logits_dev);

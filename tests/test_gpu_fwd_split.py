@@ -114,17 +114,18 @@ def test_step_of_wide_models(pm, orc, torch, F, O, B):
     net.close()
 
 
-@pytest.mark.parametrize("F,O,B", [(50, 2, 1000), (20, 3, 300), (100, 2, 513)])
-def test_forward_of_large_batches_equals_its_parts(pm, torch, F, O, B):
+@pytest.mark.parametrize("F,O,B,part", [(50, 2, 1000, 64), (20, 3, 300, 100), (100, 2, 513, 100),
+                                        (36, 2, 380, 64)])
+def test_forward_of_large_batches_equals_its_parts(pm, torch, F, O, B, part):
     """A forward pass over more than 256 samples runs them in batches of one
-    class; the parts alone, in batches of another, sum each model's units in
-    another order only."""
+    class (256, 64, 64 and 128 samples here); the parts alone, in batches of
+    another, sum each model's units in another order only."""
     hs, acts, X, _ = inputs(F, O, B, "mixed")
     net = pm.PackedMLP(F, O, hs, acts, seed=24)
     Xd = dev(torch, X)
     whole = net.forward(Xd)
     assert net.kernel_variants()["fwd_m3"][0] == "k_fwd_s"
-    parts = torch.cat([net.forward(Xd[s:s + 64]) for s in range(0, B, 64)])
+    parts = torch.cat([net.forward(Xd[s:s + part]) for s in range(0, B, part)])
     assert err_logits(whole.cpu().numpy(), parts.cpu().numpy()).max() <= TOL_STEP
     net.close()
 
@@ -290,4 +291,28 @@ def test_logits_may_lie_over_the_samples(pm, torch, F, O, B, kind):
         pm.pmlp_forward(net.handle, buf.data_ptr() + 4 * at, B, buf.data_ptr())
         got = buf[:B * M * O].reshape(B, M, O).cpu().numpy()
         assert err_logits(got, want).max() <= TOL_STEP
+    net.close()
+
+
+@pytest.mark.parametrize("M,w,F,O,B", [(900, 2, 100, 4, 5000), (300, 4, 50, 2, 10000),
+                                       (40, 3, 20, 3, 1000), (2000, 1, 36, 2, 3000),
+                                       (550, 2, 100, 2, 33100), (300, 4, 70, 2, 16500)])
+def test_many_batches_of_narrow_models(pm, orc, torch, M, w, F, O, B):
+    """Passes of many batches take runs of several models (whose logits of a
+    sample fill lines) where the pack has enough of them, and several rounds of
+    workgroups where one leaves many idle (130 batches of 256 or of 128 here);
+    against the oracle, on every model and a part of the samples."""
+    rng = np.random.default_rng(M + w)
+    hs = np.maximum(rng.integers(w - 1, w + 2, max(M, 1100 // w)), 1).astype(np.int32)
+    acts = rng.integers(0, 10, len(hs)).astype(np.int32)
+    X, _ = wl.make_dataset(F, O, B, seed=M)
+    net = pm.PackedMLP(F, O, hs, acts, seed=13)
+    W1, W2 = net.get_params()
+    got = net.forward(dev(torch, X))
+    assert net.kernel_variants()["fwd_m3"][0] == "k_fwd_s"
+    rows = np.unique(np.concatenate([np.arange(0, B, max(61, B // 60)), np.arange(B - 70, B)]))
+    want = orc.forward(hs, acts, W1, W2, X[rows])
+    assert err_logits(got[torch.from_numpy(rows).cuda()].cpu().numpy(), want).max() <= TOL_STEP
+    one = net.forward(dev(torch, X[:200]))      # and one batch, by its own groups
+    assert err_logits(one.cpu().numpy(), got[:200].cpu().numpy()).max() <= TOL_STEP
     net.close()
