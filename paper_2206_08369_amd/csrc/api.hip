@@ -532,7 +532,6 @@ hipError_t launch_fwd_s(int c, const FwdSArgs& a, hipStream_t s) {
 // units at most.  A model costs its units and about three more (its reduction
 // and its logits).
 constexpr int64_t kStepGroup = 1024;
-constexpr int64_t kSplitUnits = 1024;
 
 //
 // A pass of many batches has workgroups enough without narrow runs, and theirs
@@ -589,8 +588,7 @@ std::vector<StepGroup> step_groups(const std::vector<int32_t>& hs, int64_t N, in
 // Workgroups of class c that the device holds, or 0.
 int forward_slots(pmlp* h, int c) {
   FwdPlan& p = h->plan[c];
-  if (p.slots < 0)
-    p.slots = kStepBatch[c] >= 64 && h->N < kSplitUnits ? 0 : fwd_s_slots(c, h->F4, h->O);
+  if (p.slots < 0) p.slots = fwd_s_slots(c, h->F4, h->O);
   return p.slots;
 }
 

@@ -45,13 +45,14 @@ def dev(torch, a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-# (F, O, B, models): at least 1,024 units where the batch is above 32
+# (F, O, B, models)
 SHAPES = [
     (3, 2, 40, "mixed"), (12, 4, 64, "mixed"), (16, 3, 100, "mixed"), (30, 2, 128, "narrow"),
     (33, 4, 200, "mixed"), (48, 2, 250, "mixed"), (64, 3, 64, "narrow"), (76, 2, 129, "mixed"),
     (80, 4, 256, "narrow"), (96, 2, 100, "mixed"), (100, 2, 256, "mixed"), (104, 3, 130, "narrow"),
     (100, 4, 33, "mixed"), (50, 2, 128, "narrow"), (100, 2, 250, "many"), (100, 2, 256, "wide"),
     (104, 4, 16, "few"), (100, 2, 20, "few"), (9, 3, 1, "few"), (68, 2, 32, "mixed"),
+    (10, 2, 200, "few"), (100, 4, 64, "few"), (20, 3, 300, "few"),
 ]
 
 
