@@ -15,8 +15,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libpmlp.so")
-# (source, extra flags); the batch-resident kernels are compiled once per
-# padded batch size
+# (source, extra flags); the one-kernel forward pass is compiled once per padded
+# batch size
 SOURCES = [("k_lds.hip", [])]
 SOURCES += [("k_fwd_s.hip", ["-DPMLP_FWD_BP=%d" % bp]) for bp in (256, 128, 64, 32, 16)]
 SOURCES += [(s, []) for s in ("k_gemm_bf16.hip", "k_m3.hip", "k_misc.hip", "k_gemm.hip", "k_deep.hip",

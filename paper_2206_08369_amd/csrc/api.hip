@@ -105,14 +105,14 @@ struct PmlpDeep {
 struct FwdGroups {
   int32_t n = 0;
   int64_t cost = 0, most = 0;  // of a batch (see forward_run): all groups, the dearest
-  StepGroup* g = nullptr;
+  FwdGroup* g = nullptr;
 };
 struct FwdPlan {
   int slots = -1;  // workgroups the device holds (0: no instance, -1: not asked yet)
   FwdGroups one, many;
 };
-constexpr int kStepClasses = 5;
-constexpr int32_t kStepBatch[kStepClasses] = {16, 32, 64, 128, 256};
+constexpr int kFwdClasses = 5;
+constexpr int32_t kFwdBatch[kFwdClasses] = {16, 32, 64, 128, 256};
 
 struct pmlp {
   int dev = 0;
@@ -133,7 +133,7 @@ struct pmlp {
   int32_t* d_mid = nullptr;   // [Npad] model of each hidden unit
   int32_t* d_actn = nullptr;  // [Npad] activation id of each hidden unit
   int32_t* d_uinfo = nullptr; // [Npad] the same, + 256 at the last unit of a model (with a plan)
-  FwdPlan plan[kStepClasses];
+  FwdPlan plan[kFwdClasses];
   int32_t widest = 0;  // units of the widest model
   Tile3* d_tiles = nullptr;
   int32_t* d_order = nullptr;  // tile indices, widest first
@@ -281,9 +281,9 @@ int use_device(pmlp* h) {
   return PMLP_OK;
 }
 
-int step_class(int32_t Bp) {
-  for (int c = 0; c < kStepClasses; ++c)
-    if (kStepBatch[c] == Bp) return c;
+int batch_class(int32_t Bp) {
+  for (int c = 0; c < kFwdClasses; ++c)
+    if (kFwdBatch[c] == Bp) return c;
   return -1;
 }
 
@@ -506,7 +506,7 @@ int32_t pad_batch(int32_t B) {
 // ---- the sample-split forward ------------------------------------------------
 
 #define PMLP_BY_BATCH(c, call)   \
-  switch (kStepBatch[c]) {       \
+  switch (kFwdBatch[c]) {       \
     case 16: return call(16);    \
     case 32: return call(32);    \
     case 64: return call(64);    \
@@ -528,10 +528,10 @@ hipError_t launch_fwd_s(int c, const FwdSArgs& a, hipStream_t s) {
 }
 
 // Runs of whole models for `slots` workgroups: the widest of at most k
-// `slots` runs as narrow as can be, k such that a run is about kStepGroup
+// `slots` runs as narrow as can be, k such that a run is about kGroupUnits
 // units at most.  A model costs its units and about three more (its reduction
 // and its logits).
-constexpr int64_t kStepGroup = 1024;
+constexpr int64_t kGroupUnits = 1024;
 
 //
 // A pass of many batches has workgroups enough without narrow runs, and theirs
@@ -541,11 +541,11 @@ constexpr int64_t kStepGroup = 1024;
 // against 229 through the other kernels.
 constexpr int32_t kRunLogits = 32;
 
-std::vector<StepGroup> step_groups(const std::vector<int32_t>& hs, int64_t N, int slots,
+std::vector<FwdGroup> group_models(const std::vector<int32_t>& hs, int64_t N, int slots,
                                    int32_t least) {
   constexpr int64_t kModel = 3;
   const int64_t total = N + kModel * (int64_t)hs.size();
-  const int64_t k = ((total + slots - 1) / slots + kStepGroup - 1) / kStepGroup;
+  const int64_t k = ((total + slots - 1) / slots + kGroupUnits - 1) / kGroupUnits;
   const int64_t want = k * slots;
   auto runs = [&](int64_t cap) {  // of at most cap, filled in order
     int64_t n = 1, at = 0;
@@ -566,22 +566,22 @@ std::vector<StepGroup> step_groups(const std::vector<int32_t>& hs, int64_t N, in
     if (runs(mid) <= want) hi = mid;
     else lo = mid + 1;
   }
-  std::vector<StepGroup> g;
-  StepGroup cur{0, 0, 0, 0};
+  std::vector<FwdGroup> g;
+  FwdGroup cur{0, 0, 0, 0};
   int64_t n = 0;
   for (size_t m = 0; m < hs.size(); ++m) {
     if (cur.nm >= least && cur.len + hs[m] + kModel * (cur.nm + 1) > hi) {
       g.push_back(cur);
       cur.nm = 0;
     }
-    if (cur.nm == 0) cur = StepGroup{n, 0, (int32_t)m, 0};
+    if (cur.nm == 0) cur = FwdGroup{n, 0, (int32_t)m, 0};
     cur.len += hs[m];
     ++cur.nm;
     n += hs[m];
   }
   g.push_back(cur);
   std::stable_sort(g.begin(), g.end(),
-                   [](const StepGroup& x, const StepGroup& y) { return x.len > y.len; });
+                   [](const FwdGroup& x, const FwdGroup& y) { return x.len > y.len; });
   return g;
 }
 
@@ -601,9 +601,9 @@ int forward_slots(pmlp* h, int c) {
 bool make_groups(pmlp* h, int c, bool many) {
   FwdGroups& q = many ? h->plan[c].many : h->plan[c].one;
   if (q.g) return true;
-  const std::vector<StepGroup> g =
-      step_groups(h->hs, h->N, h->plan[c].slots, many ? div_up(kRunLogits, h->O) : 1);
-  const size_t bytes = g.size() * sizeof(StepGroup);
+  const std::vector<FwdGroup> g =
+      group_models(h->hs, h->N, h->plan[c].slots, many ? div_up(kRunLogits, h->O) : 1);
+  const size_t bytes = g.size() * sizeof(FwdGroup);
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   hipStream_t s = h->stream;
@@ -614,7 +614,7 @@ bool make_groups(pmlp* h, int c, bool many) {
     s = nullptr;
     ok = hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess;
   }
-  StepGroup* groups = nullptr;
+  FwdGroup* groups = nullptr;
   int32_t* uinfo = nullptr;
   ok = ok && hipMalloc(&groups, bytes) == hipSuccess &&
        hipMemcpyAsync(groups, g.data(), bytes, hipMemcpyHostToDevice, s) == hipSuccess;
@@ -635,8 +635,8 @@ bool make_groups(pmlp* h, int c, bool many) {
   q.g = groups;
   q.n = (int32_t)g.size();
   q.cost = q.most = 0;
-  for (const StepGroup& x : g) {
-    const int64_t tiles = div_up(x.len, 16), stages = div_up(tiles, std::max(1, kStepBatch[c] / 32));
+  for (const FwdGroup& x : g) {
+    const int64_t tiles = div_up(x.len, 16), stages = div_up(tiles, std::max(1, kFwdBatch[c] / 32));
     const int64_t v = 16 * (tiles + stages) + 3 * x.nm;
     q.cost += v;
     q.most = std::max(q.most, v);
@@ -702,18 +702,18 @@ FwdRun forward_run(pmlp* h, int c, int64_t nchunk) {
 // 300 (of 320 / 384 / 512) 36 / 38 / 46; 334 models of 21 units, one feature, 392
 // samples (of 448 / 512 / 512) 10 / 14 / 14.
 int forward_class(pmlp* h, int32_t B, int32_t Bp, int32_t* nchunk) {
-  const int one = step_class(Bp);
+  const int one = batch_class(Bp);
   *nchunk = 1;
   if (one >= 0) return forward_slots(h, one) > 0 ? one : -1;
   const bool full = h->N * B >= (int64_t)1 << 26;
   int best = -1;
   double least = 0;
-  for (int c = 2; c < kStepClasses; ++c) {
-    const int nw = kStepBatch[c] / 32, slots = forward_slots(h, c);
+  for (int c = 2; c < kFwdClasses; ++c) {
+    const int nw = kFwdBatch[c] / 32, slots = forward_slots(h, c);
     if (slots <= 0) continue;
-    const int32_t n = div_up(B, kStepBatch[c]);
+    const int32_t n = div_up(B, kFwdBatch[c]);
     const bool three = slots * nw >= 3 * 1024;  // (of 1,024 SIMDs)
-    double cost = (double)n * kStepBatch[c];
+    double cost = (double)n * kFwdBatch[c];
     if (full) cost *= (1 + 1.0 / nw) / (three ? 1.2 : 1.0);
     if (best >= 0 && cost > least) continue;
     least = cost;
@@ -734,8 +734,8 @@ int forward_class(pmlp* h, int32_t B, int32_t Bp, int32_t* nchunk) {
 // batches of 16, widths up to 64 and 100, 19 / 11 and 19 / 16; up to 200, 20 /
 // 24 (stays).
 bool fwd_split_pays(const pmlp* h, int c, int64_t nchunk) {
-  if (h->fused_forward && fwd_m3_supported(kStepBatch[c], h->F4, h->O)) return false;
-  return h->widest <= 128 + h->N * kStepBatch[c] * nchunk / 50000;
+  if (h->fused_forward && fwd_m3_supported(kFwdBatch[c], h->F4, h->O)) return false;
+  return h->widest <= 128 + h->N * kFwdBatch[c] * nchunk / 50000;
 }
 
 // The sample-split forward of B samples in nchunk batches of class c: logits

@@ -37,7 +37,7 @@ namespace {
 // the model's end.  A model's samples belong to one wave each, so no sum
 // crosses a wave and there are no atomics.
 //
-// Workgroups take groups of whole models (the step plans), wide ones first,
+// Workgroups take groups of whole models (the handle's plans), wide ones first,
 // forwards and backwards in turn, which leaves their loads within a group of
 // each other.
 //
@@ -45,11 +45,10 @@ namespace {
 // and the vector work (activation, sums, splitting) are about half of the time
 // each: with two waves per SIMD they overlap in part only.  In packs below
 // some 50,000 units the launch is one workgroup's chain: X from memory and its
-// pieces 8 us, then 0.1 us per unit.  Measured, us, the product, the clearing
-// of the logits and the M3 forward / this kernel: 60 models x 1 sample, 10
-// features, 20 / 8; 50,500 units x 10,000 samples, 50 features, 1993 / 867;
-// 505,000 x 256, 100 features, 331 / 226; 5,000,000 x 256, widths up to 1,000,
-// 2650 / 2080.
+// pieces 8 us, then 0.1 us per unit.  Measured, us a call, batch copy, product
+// and M3 forward / this kernel: 60 models x 1 sample, 10 features, 15 / 7; 50,500
+// units x 10,000 samples, 50 features, 1948 / 628; 505,000 x 256, 100 features,
+// 341 / 227; 5,005,000 x 256, widths up to 1,000, 2748 / 1953.
 //
 // The six products hold an fp32 product as long as no piece and no partial sum
 // leaves the range of fp32.  An infinite operand has NaN for its second piece,
@@ -66,11 +65,13 @@ namespace {
 // 0.9e-7, 100 features and 16 or 64 samples 1.9e-7 / 1.5e-7 (120 models of 1 to
 // 100 units).  (A piece of an operand below 1e-33 is subnormal.)
 //
-// Training steps stay on the unit-split kernels.  With Z stored as well this
-// kernel took 2410 us of the last of these (5.1 GB of stores) and made an epoch
-// of 1,000 models a fifth shorter, but an epoch's parameters then carry another
-// rounding of every step: samples that end up on the other side of ReLU's kink
-// moved single weights of narrow models by up to 4.7e-4 of the weights' rms.
+// Training steps stay on the unit-split kernels, by choice: with Z stored as well
+// this kernel took 2410 us of the last of these (5.1 GB of stores) and made an
+// epoch of 1,000 models a fifth shorter, at the same error against 64 bits, but
+// an epoch's parameters would then carry another rounding of every step (samples
+// that end up on the other side of ReLU's kink moved single weights of narrow
+// models by up to 4.7e-4 of the weights' rms), and trained pools stay the same
+// bits as long as no error is at stake.
 // ---------------------------------------------------------------------------
 
 constexpr int kBp = PMLP_FWD_BP;
@@ -87,32 +88,32 @@ struct FwdShape {
   static constexpr int RM = TQ & 1 ? 3 : 0;
 };
 
-constexpr int kStepOne = 256, kStepEnd = 512;  // bits of a tile's word
-constexpr int kStepLast = 256;                 // bit of a unit's uinfo
-constexpr int kStepPad = 512;                  // of a tile's row past its group
+constexpr int kTileOne = 256, kTileEnd = 512;  // bits of a tile's word
+constexpr int kUnitLast = 256;                 // bit of a unit's uinfo
+constexpr int kRowPad = 512;                  // of a tile's row past its group
 
 __host__ __device__ constexpr int fwd_tile_bytes(int NC, int rem, int OM) {
   return NC * 3072 + rem * 256 + 64 * (1 + OM) + 16;
 }
 
 template <class T>
-__device__ __forceinline__ T step_opaque(T v) {
+__device__ __forceinline__ T opaque_v(T v) {
   asm volatile("" : "+v"(v));
   return v;
 }
 
 template <class T>
-__device__ __forceinline__ T step_opaque_s(T v) {
+__device__ __forceinline__ T opaque_s(T v) {
   asm volatile("" : "+s"(v));
   return v;
 }
 
 // The batch X [B][F] of one workgroup's samples as rows of F4 floats in LDS,
-// with the constant input and the zero padding: both phases take their
-// operands from it.  All of a thread's loads are in flight at once (a round
+// with the constant input and the zero padding: the waves take their pieces
+// from it.  All of a thread's loads are in flight at once (a round
 // trip takes 2 us while the other workgroups stream).
 template <int TQ, int BP, int NW>
-__device__ __forceinline__ void step_stage_x(float* xs, const float* X, int F, int F4, int bcol,
+__device__ __forceinline__ void stage_x(float* xs, const float* X, int F, int F4, int bcol,
                                              int B, int tid) {
   constexpr int NT = 64 * NW, NX = 16 * TQ * BP / NT;
   const int db = NT / F4, df = NT - db * F4;
@@ -130,8 +131,8 @@ __device__ __forceinline__ void step_stage_x(float* xs, const float* X, int F, i
       ++b;
     }
   }
-  b = step_opaque(b1);  // (the comparisons again, rather than kept in scalar registers)
-  f = step_opaque(f1);
+  b = opaque_v(b1);  // (the comparisons again, rather than kept in scalar registers)
+  f = opaque_v(f1);
 #pragma unroll
   for (int i = 0; i < NX; ++i) {
     const float w = b < B ? (f < F ? v[i] : (f == bcol ? 1.f : 0.f)) : 0.f;
@@ -149,7 +150,7 @@ __device__ __forceinline__ void step_stage_x(float* xs, const float* X, int F, i
 // `step` selects (8, 4, 2, 1): xor 8, xor 7 (row_half_mirror), xor 2, xor 1.
 // For a sum over 16 lanes in that order each lane meets every other once.
 template <int STEP>
-__device__ __forceinline__ float step_partner(float v) {
+__device__ __forceinline__ float row_partner(float v) {
   constexpr int ctrl = STEP == 8 ? 0x128 : STEP == 4 ? 0x141 : STEP == 2 ? 0x4E : 0xB1;
   return __int_as_float(
       __builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true));
@@ -159,7 +160,7 @@ __device__ __forceinline__ float step_partner(float v) {
 // lane li ends with the sums of values li V/16 .. + V/16 - 1 in v[0 ..];
 // with V = 8 lanes 2i and 2i + 1 both end with that of value i.
 template <int V, int STEP>
-__device__ __forceinline__ void step_reduce(float* v, int li) {
+__device__ __forceinline__ void row_reduce(float* v, int li) {
   constexpr bool halve = V > 1;
   const bool up = (li & STEP) != 0;
   if constexpr (halve) {
@@ -167,31 +168,31 @@ __device__ __forceinline__ void step_reduce(float* v, int li) {
     for (int q = 0; q < V / 2; ++q) {
       const float keep = up ? v[q + V / 2] : v[q];
       const float send = up ? v[q] : v[q + V / 2];
-      v[q] = keep + step_partner<STEP>(send);
+      v[q] = keep + row_partner<STEP>(send);
     }
   } else {
-    v[0] += step_partner<STEP>(v[0]);
+    v[0] += row_partner<STEP>(v[0]);
   }
-  if constexpr (STEP > 1) step_reduce<(halve ? V / 2 : 1), STEP / 2>(v, li);
+  if constexpr (STEP > 1) row_reduce<(halve ? V / 2 : 1), STEP / 2>(v, li);
 }
 
 // Activation id `act` (uniform over the wave below 255, else each lane's own
 // arow) of NV values, in place.  Rows of several activations take the same
 // code once per activation.
-#define PMLP_STEP_ACTS                                                                      \
+#define PMLP_ACTS                                                                      \
   PMLP_ACT(0) PMLP_ACT(1) PMLP_ACT(2) PMLP_ACT(3) PMLP_ACT(4) PMLP_ACT(5) PMLP_ACT(6)       \
   PMLP_ACT(7) PMLP_ACT(8) PMLP_ACT(9) PMLP_ACT(10) PMLP_ACT(11) PMLP_ACT(12)
 
 // act_fwd, with KEEP NaN for NaN also where its choice of a branch drops it.
 template <bool KEEP>
-__device__ __forceinline__ float step_act_fwd(int a, float z) {
+__device__ __forceinline__ float tile_act_fwd(int a, float z) {
   if (KEEP && a == 1) return z <= 0.f ? 0.f : z;
   if (KEEP && a == 11) return fabsf(z) <= 0.5f ? 0.f : z;
   return act_fwd(a, z);
 }
 
 template <bool KEEP, int NV>
-__device__ __forceinline__ void step_act(int act, int arow, float (&z)[NV]) {
+__device__ __forceinline__ void tile_act(int act, int arow, float (&z)[NV]) {
   const bool one = act < 255;
   int A = one ? act : __builtin_amdgcn_readfirstlane(arow);
   bool done = false;
@@ -200,14 +201,14 @@ __device__ __forceinline__ void step_act(int act, int arow, float (&z)[NV]) {
     float v[NV];
     // (opaque, or every activation's terms would be hoisted out of the loop)
 #pragma unroll
-    for (int j = 0; j < NV; ++j) z[j] = step_opaque(z[j]);
+    for (int j = 0; j < NV; ++j) z[j] = opaque_v(z[j]);
     switch (A) {
 #define PMLP_ACT(AA)                                                         \
   case AA: {                                                                 \
-    _Pragma("unroll") for (int j = 0; j < NV; ++j) v[j] = step_act_fwd<KEEP>(AA, z[j]); \
+    _Pragma("unroll") for (int j = 0; j < NV; ++j) v[j] = tile_act_fwd<KEEP>(AA, z[j]); \
     break;                                                                   \
   }
-      PMLP_STEP_ACTS
+      PMLP_ACTS
 #undef PMLP_ACT
     }
     if (one) {
@@ -230,7 +231,7 @@ __device__ __forceinline__ void step_act(int act, int arow, float (&z)[NV]) {
 // each lane's).
 constexpr int kRedo = 4;  // steps whose loads are in flight
 template <int OM>
-__device__ __forceinline__ void step_model_fp32(const FwdSArgs& a, int m, int b0, int li, int lk) {
+__device__ __forceinline__ void model_fp32(const FwdSArgs& a, int m, int b0, int li, int lk) {
   // value `idx` of a lane's 4 OM sums after the reduction over the 16 li
   const int idx = OM == 2 ? li >> 1 : li, o1 = idx % OM, b1 = b0 + 4 * lk + idx / OM;
   float* const dst = a.out + (int64_t)m * a.sm + (int64_t)b1 * a.sb + o1;
@@ -272,7 +273,7 @@ __device__ __forceinline__ void step_model_fp32(const FwdSArgs& a, int m, int b0
     float h[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) h[r] = in ? acc[r] : 0.f;
-    step_act<false>(act, 0, h);
+    tile_act<false>(act, 0, h);
 #pragma unroll
     for (int r = 0; r < 4; ++r) h[r] = in ? h[r] : 0.f;
 #pragma unroll
@@ -282,7 +283,7 @@ __device__ __forceinline__ void step_model_fp32(const FwdSArgs& a, int m, int b0
       for (int r = 0; r < 4; ++r) S[r * OM + o] = fmaf(h[r], in ? w2 : 0.f, S[r * OM + o]);
     }
   }
-  step_reduce<4 * OM, 8>(S, li);
+  row_reduce<4 * OM, 8>(S, li);
   if (mine && !(OM == 2 && (li & 1))) *dst = S[0] + (a.b2 ? a.b2[(int64_t)m * a.O + o1] : 0.f);
 }
 
@@ -309,7 +310,7 @@ void k_fwd_s(FwdSArgs a) {
   bf16x8 x0[NI][NC > 0 ? NC : 1], x1[NI][NC > 0 ? NC : 1], x2[NI][NC > 0 ? NC : 1];
   float xt[NI][RM > 0 ? RM : 1];
   float* const xs = (float*)lds;
-  step_stage_x<TQ, BP, NW>(xs, a.X + (int64_t)chunk * BP * a.F, a.F, F4, a.bcol, B, threadIdx.x);
+  stage_x<TQ, BP, NW>(xs, a.X + (int64_t)chunk * BP * a.F, a.F, F4, a.bcol, B, threadIdx.x);
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
@@ -347,7 +348,7 @@ void k_fwd_s(FwdSArgs a) {
     p.m0 = 0;
     p.n0 = 0;
     if (g < a.ngroups) {
-      const StepGroup q = a.groups[g];
+      const FwdGroup q = a.groups[g];
       p.n0 = q.n0;
       p.len = q.len;
       p.m0 = q.m0;
@@ -394,15 +395,15 @@ void k_fwd_s(FwdSArgs a) {
     for (int q = 0; q < RM; ++q)
       r.t[q] = wt[wo + (uint32_t)(32 * NC + 4 * (q < rem ? q : 0) + lk)];
     const int info = (a.uinfo + p0)[row];
-    r.info = (in ? info : (info & 255) | kStepPad) | (((a.mid + p0)[row] - p.m0) << 10);
+    r.info = (in ? info : (info & 255) | kRowPad) | (((a.mid + p0)[row] - p.m0) << 10);
 #pragma unroll
     for (int o = 0; o < OM; ++o)
       r.w2[o] = in && o < a.O ? (a.W2 + ((int64_t)o * a.ldw + p0))[row] : 0.f;
   };
   auto put = [&](Raw& r, int buf) {
     char* base = lds + (buf * ST + wave) * TB;
-    if (__any(r.info & kStepPad)) {
-      const bool pad = r.info & kStepPad;
+    if (__any(r.info & kRowPad)) {
+      const bool pad = r.info & kRowPad;
 #pragma unroll
       for (int c = 0; c < 2 * NC; ++c)
 #pragma unroll
@@ -425,8 +426,8 @@ void k_fwd_s(FwdSArgs a) {
     const int i0 = __builtin_amdgcn_readfirstlane(r.info);
     // one activation (else 255), one model, a model's last unit
     const int word = (__all(((r.info ^ i0) & 255) == 0) ? i0 & 255 : 255) |
-                     (__all((r.info >> 10) == (i0 >> 10)) ? kStepOne : 0) |
-                     (__any(r.info & kStepLast) ? kStepEnd : 0);
+                     (__all((r.info >> 10) == (i0 >> 10)) ? kTileOne : 0) |
+                     (__any(r.info & kUnitLast) ? kTileEnd : 0);
     if (lk == 0) {
       int* mt = (int*)(base + NC * 3072 + rem * 256) + li;
       mt[0] = r.info;
@@ -441,7 +442,7 @@ void k_fwd_s(FwdSArgs a) {
   uint64_t bad = 0;  // bit m % 64: a logit of model m is NaN
   // the open model ends: its logits, and the sums start again
   auto emit = [&](int mm) {
-    step_reduce<V * OM, 8>(S, li);
+    row_reduce<V * OM, 8>(S, li);
     constexpr int PER = V * OM >= 16 ? V * OM / 16 : 1;  // values per lane
     const int idx0 = V * OM >= 16 ? li * PER : li >> 1;
     float* const dst = a.out + (int64_t)chunk * BP * a.sb + (int64_t)mm * a.sm;
@@ -515,18 +516,18 @@ _Pragma("unroll") for (int i = 0; i < NI; ++i) acc[i] = \
         float h[V];
 #pragma unroll
         for (int q = 0; q < V; ++q) h[q] = acc[q >> 2][q & 3];
-        step_act<NC != 0>(word & 255, (word & 255) == 255 ? mt[li] & 255 : 0, h);
-        if (word & kStepOne) {
+        tile_act<NC != 0>(word & 255, (word & 255) == 255 ? mt[li] & 255 : 0, h);
+        if (word & kTileOne) {
 #pragma unroll
           for (int q = 0; q < V; ++q)
 #pragma unroll
             for (int o = 0; o < OM; ++o) S[q * OM + o] = fmaf(h[q], w2[o], S[q * OM + o]);
-          if (word & kStepEnd)
+          if (word & kTileEnd)
             emit(p0.m0 + __builtin_amdgcn_readfirstlane(mt[0] >> 10));
         } else {
           // a model at a time, the other models' rows out of the sums
           const int mrow = mt[li] >> 10;
-          const bool last = mt[li] & kStepLast;
+          const bool last = mt[li] & kUnitLast;
           const int m0 = __builtin_amdgcn_readfirstlane(mrow);
           const int ml = __builtin_amdgcn_readlane(mrow, 15);
           for (int mm = m0; mm <= ml; ++mm) {
@@ -557,21 +558,21 @@ _Pragma("unroll") for (int i = 0; i < NI; ++i) acc[i] = \
     __threadfence_block();  // (a logit is read by another lane than wrote it)
     // (arguments and indices afresh: held over the stages they would cost
     // registers there)
-    const FwdSArgs& r = *(const FwdSArgs*)step_opaque_s(__builtin_amdgcn_kernarg_segment_ptr());
-    const int t = step_opaque((int)threadIdx.x), bid = step_opaque_s((int)blockIdx.x);
+    const FwdSArgs& r = *(const FwdSArgs*)opaque_s(__builtin_amdgcn_kernarg_segment_ptr());
+    const int t = opaque_v((int)threadIdx.x), bid = opaque_s((int)blockIdx.x);
     const int c = bid / r.wpc, first = bid - c * r.wpc;
     const int b0 = c * BP + 16 * NI * __builtin_amdgcn_readfirstlane(t >> 6);
 #pragma unroll 1
     for (int k = 0;; ++k) {
       const int g = k * r.wpc + (k & 1 ? r.wpc - 1 - first : first);
       if (g >= r.ngroups) break;
-      const StepGroup q = r.groups[g];
+      const FwdGroup q = r.groups[g];
 #pragma unroll 1
       for (int m = q.m0; m < q.m0 + q.nm; ++m)
         if (bad >> (m & 63) & 1)
 #pragma unroll 1
           for (int i = 0; i < NI; ++i)
-            step_model_fp32<OM>(r, m, b0 + 16 * i, t & 15, (t & 63) >> 4);
+            model_fp32<OM>(r, m, b0 + 16 * i, t & 15, (t & 63) >> 4);
     }
   }
 }
@@ -604,7 +605,7 @@ FwdSFn fwd_s_fn(int32_t F4) {
 }
 
 FwdSFn fwd_s_pick(int32_t F4, int32_t O) {
-  if (F4 < 4 || F4 > 112) return nullptr;
+  if (F4 < 4 || F4 > 108) return nullptr;
   return O <= 2 ? fwd_s_fn<2>(F4) : O <= 4 ? fwd_s_fn<4>(F4) : nullptr;
 }
 
@@ -617,7 +618,7 @@ FwdSFn fwd_s_pick(int32_t F4, int32_t O) {
 // shape has no instance or does not fit in LDS.
 int PMLP_CAT(fwd_s_slots_, PMLP_FWD_BP)(int32_t F4, int32_t O) {
   FwdSFn fn = fwd_s_pick(F4, O);
-  return fn ? resident_blocks((const void*)fn, 64 * kNW, fwd_s_lds(F4, step_om(O))) : 0;
+  return fn ? resident_blocks((const void*)fn, 64 * kNW, fwd_s_lds(F4, fwd_om(O))) : 0;
 }
 
 hipError_t PMLP_CAT(launch_fwd_s_, PMLP_FWD_BP)(const FwdSArgs& a, hipStream_t s) {
@@ -625,7 +626,7 @@ hipError_t PMLP_CAT(launch_fwd_s_, PMLP_FWD_BP)(const FwdSArgs& a, hipStream_t s
   if (!fn || a.ngroups <= 0 || a.wpc <= 0 || a.nchunk <= 0 ||
       (int64_t)a.nchunk * a.wpc > 0x7fffffff)
     return hipErrorInvalidValue;
-  fn<<<(unsigned)(a.nchunk * a.wpc), 64 * kNW, fwd_s_lds(a.F4, step_om(a.O)), s>>>(a);
+  fn<<<(unsigned)(a.nchunk * a.wpc), 64 * kNW, fwd_s_lds(a.F4, fwd_om(a.O)), s>>>(a);
   return hipGetLastError();
 }
 

@@ -196,7 +196,7 @@ inline int resident_blocks(const void* fn, int threads, size_t lds) {
 }
 
 // Groups of whole models, the work units of k_fwd_s.
-struct StepGroup {
+struct FwdGroup {
   int64_t n0;           // first hidden unit
   int32_t len;          // hidden units
   int32_t m0, nm;       // first model, number of models
@@ -216,7 +216,7 @@ struct FwdSArgs {
   const int32_t* mid;    // [Npad] model of each unit
   const int32_t* uinfo;  // [Npad] activation id, + 256 at a model's last unit
   const int64_t* seg_off;  // [M+1] first unit of each model
-  const StepGroup* groups;
+  const FwdGroup* groups;
   int32_t ngroups;
   float* out;
   int64_t sm, sb;
@@ -232,7 +232,7 @@ PMLP_FWD_S_DECL(256)
 #undef PMLP_FWD_S_DECL
 
 // Outputs per model as k_fwd_s sums them.
-inline int step_om(int32_t O) { return O <= 2 ? 2 : 4; }
+inline int fwd_om(int32_t O) { return O <= 2 ? 2 : 4; }
 
 hipError_t launch_init_params(float* W1, int64_t N, int32_t F, int32_t F4, float bound1,
                               float* W2, int64_t ldw, int32_t O, const int32_t* mid,
