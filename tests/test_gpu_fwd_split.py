@@ -317,3 +317,20 @@ def test_many_batches_of_narrow_models(pm, orc, torch, M, w, F, O, B):
     one = net.forward(dev(torch, X[:200]))      # and one batch, by its own groups
     assert err_logits(one.cpu().numpy(), got[:200].cpu().numpy()).max() <= TOL_STEP
     net.close()
+
+
+@pytest.mark.parametrize("F,biases,one", [(108, False, True), (109, False, False),
+                                          (112, False, False), (104, True, True),
+                                          (105, True, False)])
+def test_the_widest_input(pm, orc, torch, F, biases, one):
+    """The kernel takes rows of up to 108 floats (the bias has four of its own);
+    wider ones take the other kernels, with the same logits."""
+    hs, acts, X, _ = inputs(F, 2, 100, "mixed")
+    net = pm.PackedMLP(F, 2, hs, acts, seed=6, biases=biases)
+    W1, W2 = net.get_params()
+    if biases:
+        net.set_biases(np.zeros(int(hs.sum()), np.float32), np.zeros((len(hs), 2), np.float32))
+    got = net.forward(dev(torch, X)).cpu().numpy()
+    assert (net.kernel_variants()["fwd_m3"][0] == "k_fwd_s") == one
+    assert err_logits(got, orc.forward(hs, acts, W1, W2, X)).max() <= TOL_STEP
+    net.close()

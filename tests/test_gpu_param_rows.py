@@ -1,11 +1,13 @@
 """Parameters to and from the host: packed rows through the staging buffer
 (rows narrower than their stride, in one piece and in several), contiguous
 rows, wide rows, and the one-column bias rows.  Values written come back bit
-for bit, and the padding between rows stays what training needs it to be."""
+for bit, and the padding between rows stays what training needs it to be: a
+forward pass and a gradient step after parameters were set equal the oracle's."""
 import numpy as np
 import pytest
 
 import pmlp_workloads as wl
+from parity import err_logits, err_losses, err_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -55,4 +57,32 @@ def test_two_layer_round_trip(pm):
     net.set_params(*W)
     for a, b in zip(net.get_params(), W):
         assert np.array_equal(a, b)
+    net.close()
+
+
+@pytest.mark.parametrize("F,biases", [(1, False), (3, True), (50, False), (50, True), (150, False)])
+def test_padding_between_rows(pm, orc, F, biases):
+    import torch
+    rng = np.random.default_rng(F)
+    hs = rng.integers(1, 60, 50).astype(np.int32)
+    acts = (np.arange(50) % 10).astype(np.int32)
+    N, O, B = int(hs.sum()), 3, 140
+    X, y = wl.make_dataset(F, O, B, seed=F)
+    net = pm.PackedMLP(F, O, hs, acts, seed=2, biases=biases)
+    for _ in range(2):                      # the second time over used rows
+        W1 = rng.uniform(-0.5, 0.5, (N, F)).astype(np.float32)
+        W2 = rng.uniform(-0.5, 0.5, (O, N)).astype(np.float32)
+        kw = {}
+        net.set_params(W1, W2)
+        if biases:
+            kw = dict(b1=rng.uniform(-0.5, 0.5, N).astype(np.float32),
+                      b2=rng.uniform(-0.5, 0.5, (50, O)).astype(np.float32))
+            net.set_biases(kw["b1"], kw["b2"])
+        Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+        got = net.forward(Xd).cpu().numpy()
+        assert err_logits(got, orc.forward(hs, acts, W1, W2, X, **kw)).max() <= 1e-5
+        g1 = net.gradients(Xd, yd)[0].cpu().numpy()
+        ref = orc.gradients(hs, acts, W1, W2, X, y, **kw)
+        assert err_rows(g1, ref[0], hs, ref[3]).max() <= 1e-5
+        assert err_losses(net.losses(), ref[2]).max() <= 1e-5
     net.close()
