@@ -51,7 +51,11 @@
  *   - A handle is not thread-safe; use one handle per thread or serialise.
  *   - Sizes: B >= 1 samples per batch; rows of X_dev are F contiguous
  *     floats (row stride F).  Batches of any size up to 2^20 are accepted;
- *     internal workspaces grow to the largest batch seen.
+ *     internal workspaces grow to the largest batch that a call needing
+ *     them has seen.  A pmlp_forward that runs in one kernel (see
+ *     pmlp_set_precision) needs none, so under HIP graph capture a
+ *     training, gradient or hidden call wants an earlier one of its own
+ *     batch size; pmlp_forward in one kernel wants none.
  */
 #ifndef PMLP_H
 #define PMLP_H
