@@ -29,6 +29,17 @@ setting (for instance PMLP_FUSED_FORWARD=1) and the files are named for
 WORKLOAD_L.
 
 usage: python bench_profiles.py OUTDIR WORKLOAD [PRECISION] [--label L --env NAME=VALUE]
+
+The performance cases (perf/cases.py) have a trace each, and counter passes A
+and B where listed; --run makes PASSES passes of a case on the GPU, --cases
+reads OUTDIR/CASE/{trace,A,B} and writes kernel_trace_cases.md and
+counters_cases.md:
+
+  rocprofv3 --kernel-trace --stats -f csv -d $O/CASE/trace -o run -- \\
+      python3 $R/bench_profiles.py --run CASE PASSES
+
+usage: python bench_profiles.py --run CASE PASSES
+       python bench_profiles.py --cases OUTDIR CASE [CASE ...]
 """
 from __future__ import annotations
 
@@ -61,7 +72,8 @@ ROLE = {
     "k_m3_fwd": "m3_fwd",
     "k_m3_fwd_mf": "m3_fwd", "k_ce": "ce", "k_mse": "ce",
     "k_bwd_lds": "bwd_fused", "k_bwd_x3": "bwd_fused", "k_bwd_mf": "bwd_fused",
-    "k_m3_bwd": "m3_bwd", "k_w1_to_bf16": "aux",
+    "k_m3_bwd": "m3_bwd", "k_w1_to_bf16": "aux", "k_seg_fwd": "hidden2", "k_seg_grad": "hidden2",
+    "k_seg_back": "hidden2", "k_sgd": "hidden2", "k_copy_rows": "aux", "k_unit_info": "aux",
 }
 
 SET_A = ("SQ_WAVES SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU "
@@ -127,7 +139,75 @@ def mean(v):
     return sum(v) / len(v) if v else float("nan")
 
 
+def run_case(name: str, passes: int) -> int:
+    import torch
+    from perf import cases
+    case = {c["name"]: c for c in cases.listed()}[name]
+    state = cases.prepare(case, 3)
+    for _ in range(passes):
+        cases.run(state)
+        torch.cuda.synchronize()
+    print("%s: %d passes" % (name, passes), flush=True)
+    return 0
+
+
+CASES_HOW = (
+    "One MI355X, from /tmp with TMPDIR=/tmp; $R = repository root:\n\n```\n"
+    "rocprofv3 --kernel-trace --stats -f csv -d $O/CASE/trace -o run -- "
+    "python3 $R/bench_profiles.py --run CASE 4\n"
+    "rocprofv3 --pmc %s --kernel-trace -f csv -d $O/CASE/A -o run -- "
+    "python3 $R/bench_profiles.py --run CASE 4\n"
+    "rocprofv3 --pmc %s --kernel-trace -f csv -d $O/CASE/B -o run -- "
+    "python3 $R/bench_profiles.py --run CASE 4\n"
+    "python3 $R/bench_profiles.py --cases $O %s\n```\n")
+
+
+def cases_summary(outdir: str, names) -> int:
+    how = CASES_HOW % (SET_A, SET_B, " ".join(names))
+    tl = ["# Kernel traces of the performance cases\n", how,
+          "The library's kernels in four passes of each case (handles made within the run):\n"]
+    cl = ["# Counters of the performance cases\n", how,
+          "Per kernel, means over its dispatches; columns as in `counters_w10k_f100.md`.\n"]
+    for name in names:
+        sub = os.path.join(outdir, name)
+        tr = kernel_trace(sub)
+        own = {n: d for n, d in tr.items() if n.startswith("k_") and not n.startswith("k_init")}
+        total = sum(sum(d) for d in own.values())
+        tl += ["## `%s`\n" % name, "| kernel (role) | calls | avg (us) | min (us) | max (us) | % |",
+               "|---|---:|---:|---:|---:|---:|"]
+        for n, d in sorted(own.items(), key=lambda kv: -sum(kv[1])):
+            tl.append("| `%s` (%s) | %d | %.1f | %.1f | %.1f | %.1f |" % (
+                n, role_of(n, "") or "", len(d), mean(d), min(d), max(d), 100.0 * sum(d) / total))
+        tl.append("")
+        ca, cb = counters(sub, "A"), counters(sub, "B")
+        if not ca:
+            continue
+        simds, nxcc = agent(sub)
+        cl += ["## `%s`\n" % name, "| kernel | MFMA busy | VALU busy | issue wait | s_waitcnt | "
+               "LDS conflicts | VALU instr / wave | waves |", "|---|---:|---:|---:|---:|---:|---:|---:|"]
+        for n in sorted(own, key=lambda n: -sum(own[n])):
+            a, bb = ca.get(n), cb.get(n)
+            if not a or not bb:
+                continue
+            t = mean(a["GRBM_GUI_ACTIVE"]) / nxcc * simds
+            wc = max(mean(a["SQ_WAVE_CYCLES"]), 1.0)
+            cl.append("| `%s` | %.2f | %.2f | %.2f | %.2f | %.3f | %.0f | %.0f |" % (
+                n, mean(a["SQ_VALU_MFMA_BUSY_CYCLES"]) / t, 4 * mean(a["SQ_ACTIVE_INST_VALU"]) / t,
+                mean(a["SQ_WAIT_INST_ANY"]) / wc, mean(bb["SQ_WAIT_ANY"]) / wc,
+                mean(a["SQ_LDS_BANK_CONFLICT"]) / max(mean(a["SQ_ACTIVE_INST_LDS"]), 1.0),
+                mean(bb["SQ_INSTS_VALU"]) / max(mean(a["SQ_WAVES"]), 1.0), mean(a["SQ_WAVES"])))
+        cl.append("")
+    for stem, lines in (("kernel_trace", tl), ("counters", cl)):
+        with open(os.path.join(ROOT, "profiles", stem + "_cases.md"), "w") as f:
+            f.write("\n".join(lines).rstrip() + "\n")
+    return 0
+
+
 def main(argv):
+    if len(argv) == 3 and argv[0] == "--run":
+        return run_case(argv[1], int(argv[2]))
+    if len(argv) > 2 and argv[0] == "--cases":
+        return cases_summary(argv[1], argv[2:])
     if len(argv) < 2:
         print(__doc__)
         return 2
