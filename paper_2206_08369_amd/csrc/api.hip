@@ -621,7 +621,7 @@ bool make_groups(pmlp* h, int c, bool many) {
   if (!h->d_uinfo)
     ok = ok && hipMalloc(&uinfo, (size_t)h->Npad * sizeof(int32_t)) == hipSuccess &&
          launch_unit_info(h->d_mid, h->d_actn, h->N, h->Npad, uinfo, s) == hipSuccess;
-  if (!beside || s) ok = hipStreamSynchronize(s) == hipSuccess && ok;  // (g is read until here)
+  if (groups) ok = hipStreamSynchronize(s) == hipSuccess && ok;  // (g is read until here)
   if (beside) {
     if (s) (void)hipStreamDestroy(s);
     (void)hipThreadExchangeStreamCaptureMode(&mode);
