@@ -732,9 +732,15 @@ int forward_class(pmlp* h, int32_t B, int32_t Bp, int32_t* nchunk) {
 // 256, 102 / 109 (stays); 300,000 x 256, 224 / 162; 300,000 x 64, 111 / 121
 // (stays) and widths up to 400, 83 / 63; packs of 1,000 to 20,000 units and
 // batches of 16, widths up to 64 and 100, 19 / 11 and 19 / 16; up to 200, 20 /
-// 24 (stays).
+// 24 (stays).  At 128 samples, 108 columns and three or four outputs LDS leaves
+// one workgroup to a CU, one wave to a SIMD, which is too few for large packs of
+// narrow models alone (78 to 100 samples: 205,000 of 1..28, GELU, 99 / 121, stays;
+// 255,000 of 1..100, 138 / 123; 233,000 of 115, ReLU, 164 / 88; 50,500 of 1..100,
+// 62 / 37).
 bool fwd_split_pays(const pmlp* h, int c, int64_t nchunk) {
   if (h->fused_forward && fwd_m3_supported(kFwdBatch[c], h->F4, h->O)) return false;
+  const int waves = h->plan[c].slots * std::max(1, kFwdBatch[c] / 32);
+  if (nchunk == 1 && waves <= 1024 && h->N > 100000 && h->N < 32 * (int64_t)h->M) return false;
   return h->widest <= 128 + h->N * kFwdBatch[c] * nchunk / 50000;
 }
 

@@ -334,3 +334,20 @@ def test_the_widest_input(pm, orc, torch, F, biases, one):
     assert (net.kernel_variants()["fwd_m3"][0] == "k_fwd_s") == one
     assert err_logits(got, orc.forward(hs, acts, W1, W2, X)).max() <= TOL_STEP
     net.close()
+
+
+def test_large_narrow_packs_at_one_wave_per_simd(pm, orc, torch):
+    """108 columns, four outputs and 128 samples leave one workgroup to a CU: a
+    large pack of narrow models takes the other kernels there, and the one kernel
+    at 64 samples; both against the oracle on a sample of the models."""
+    hs, acts, X, _ = inputs(108, 4, 100, "many")
+    assert hs.sum() > 100000 and hs.mean() < 32
+    net = pm.PackedMLP(108, 4, hs, acts, seed=9)
+    W1, W2 = net.get_params()
+    models, _, hs_s, ac_s, W1_s, W2_s = sampled(hs, acts, W1, W2, "many")
+    for B, one in ((100, False), (64, True)):
+        got = net.forward(dev(torch, X[:B])).cpu().numpy()
+        assert (net.kernel_variants()["fwd_m3"][0] == "k_fwd_s") == one
+        want = orc.forward(hs_s, ac_s, W1_s, W2_s, X[:B])
+        assert err_logits(got[:, models], want).max() <= TOL_STEP
+    net.close()
