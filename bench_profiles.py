@@ -237,9 +237,9 @@ def main(argv):
 
     # kernel trace
     tr = kernel_trace(outdir)
-    lines = [head % "Kernel trace", "Command (one MI355X, from /tmp with TMPDIR=/tmp; $R = repository root):", "",
-             "```", envp + "rocprofv3 --kernel-trace --stats -f csv -d $R/gpurun_out/prof/%s/trace -o run -- \\" % tag,
-             "    python3 $R/bench.py %s" % args, "python3 $R/bench_profiles.py $R/gpurun_out/prof/%s %s %s%s"
+    lines = [head % "Kernel trace", "Command (one MI355X, from /tmp with TMPDIR=/tmp; $R = repository root, $O = an output directory):", "",
+             "```", envp + "rocprofv3 --kernel-trace --stats -f csv -d $O/%s/trace -o run -- \\" % tag,
+             "    python3 $R/bench.py %s" % args, "python3 $R/bench_profiles.py $O/%s %s %s%s"
              % (tag, wk, prec, (" --label %s --env %s" % (label, env)) if label else ""), "```", "",
              "Every launch of the run (warm-up epoch, timed steps and the profiled epoch, full batches only):", "",
              "| kernel (role) | calls | avg (us) | min (us) | max (us) | % of GPU time |",
@@ -273,11 +273,11 @@ def main(argv):
     simds, nxcc = agent(outdir)
     lines = [head % "Counters", "Two counter passes, each in its own run (arguments of bench.py as in "
              "`kernel_trace_%s.md`):" % tag, "", "```",
-             envp + "rocprofv3 --pmc %s --kernel-trace -f csv -d $R/gpurun_out/prof/%s/A -o run -- python3 $R/bench.py %s"
+             envp + "rocprofv3 --pmc %s --kernel-trace -f csv -d $O/%s/A -o run -- python3 $R/bench.py %s"
              % (SET_A, tag, args),
-             envp + "rocprofv3 --pmc %s --kernel-trace -f csv -d $R/gpurun_out/prof/%s/B -o run -- python3 $R/bench.py %s"
+             envp + "rocprofv3 --pmc %s --kernel-trace -f csv -d $O/%s/B -o run -- python3 $R/bench.py %s"
              % (SET_B, tag, args),
-             envp + "rocprofv3 --pmc %s --kernel-trace -f csv -d $R/gpurun_out/prof/%s/C -o run -- python3 $R/bench.py %s"
+             envp + "rocprofv3 --pmc %s --kernel-trace -f csv -d $O/%s/C -o run -- python3 $R/bench.py %s"
              % (SET_C, tag, args), "```", "",
              "Per kernel, means over its dispatches.  GRBM_GUI_ACTIVE is summed over the %d XCDs, "
              "so T = GRBM_GUI_ACTIVE / %d is the kernel's active cycles.  Derived columns:" % (nxcc, nxcc), "",
@@ -339,9 +339,9 @@ def main(argv):
     tpath = os.path.join(ROOT, "profiles", "traffic.json")
     table = json.load(open(tpath)) if os.path.exists(tpath) else {}
     lines = [head % "HBM traffic per launch", "Two counter passes (KiB per dispatch), each in its own run:", "",
-             "```", envp + "rocprofv3 --pmc FETCH_SIZE --kernel-trace -f csv -d $R/gpurun_out/prof/%s/FETCH_SIZE -o run -- "
+             "```", envp + "rocprofv3 --pmc FETCH_SIZE --kernel-trace -f csv -d $O/%s/FETCH_SIZE -o run -- "
              "python3 $R/bench.py %s --copy-probe-mib 1024" % (tag, args),
-             envp + "rocprofv3 --pmc WRITE_SIZE --kernel-trace -f csv -d $R/gpurun_out/prof/%s/WRITE_SIZE -o run -- "
+             envp + "rocprofv3 --pmc WRITE_SIZE --kernel-trace -f csv -d $O/%s/WRITE_SIZE -o run -- "
              "python3 $R/bench.py %s --copy-probe-mib 1024" % (tag, args), "```", "",
              "Calibration: in the same runs bench.py sums 2 GiB (torch's reduction, a read-only "
              "stream) and fills 2 GiB (torch's fill, a write-only stream); they read FETCH_SIZE = "
